@@ -386,7 +386,9 @@ hipError_t launch_t(const AttnArgs& a0, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, int tile, hipStream_t s) {
-  if (mfma_supported(head_dim, tile, a.dense != 0, a.n_tiles, a.seq, (int64_t)a.seq * a.st))
+  const int64_t span = (int64_t)a.seq * a.st;
+  if (mfma_supported(head_dim, tile, a.dense != 0, a.n_tiles, a.seq, span) ||
+      (!a.dense && mfma_long_supported(head_dim, tile, a.n_tiles, a.seq, span)))
     return launch_attn_mfma(a, head_dim, tile, s);
   if (head_dim == 64) {
     if (tile == 4) return launch_t<64, 2>(a, s);

@@ -29,10 +29,21 @@ bool mfma_supported(int head_dim, int tile, bool dense, int n_tiles, int seq, in
          seq >= kMfmaChunk && 2 * span < ((int64_t)1 << 32);
 }
 
+bool mfma_long_supported(int head_dim, int tile, int n_tiles, int seq, int64_t span) {
+  // As mfma_supported, with a list that passes through the lanes in parts.
+  return (head_dim == 64 || head_dim == 128) && (tile == 8 || tile == 16) && n_tiles > 64 && seq >= kMfmaChunk &&
+         2 * span < ((int64_t)1 << 32);
+}
+
 const char* attn_kernel_name(const AttnArgs& a, int head_dim, int tile, int dtype) {
   if (dtype == SSBA_DT_F32) return head_dim == 64 ? "k_attn_f32<64>" : "k_attn_f32<128>";
   if (mfma_supported(head_dim, tile, a.dense != 0, a.n_tiles, a.seq, (int64_t)a.seq * a.st))
     return mfma_kernel_name(head_dim, tile, a.dense != 0, a.gated != 0);
+  if (!a.dense && mfma_long_supported(head_dim, tile, a.n_tiles, a.seq, (int64_t)a.seq * a.st)) {
+    static const char* const longs[2][2] = {{"k_attn_mfma_long<64, 3>", "k_attn_mfma_long<64, 4>"},
+                                            {"k_attn_mfma_long<128, 3>", "k_attn_mfma_long<128, 4>"}};
+    return longs[head_dim == 64 ? 0 : 1][tile == 16 ? 1 : 0];
+  }
   static const char* const names[2][3] = {
       {"k_attn_bf16<64, 2>", "k_attn_bf16<64, 3>", "k_attn_bf16<64, 4>"},
       {"k_attn_bf16<128, 2>", "k_attn_bf16<128, 3>", "k_attn_bf16<128, 4>"}};

@@ -1,0 +1,96 @@
+"""bf16 attention with more than 64 blocks per head: kept lists that end at,
+just before and just after the 64 entries that pass through the lanes at a
+time, uneven lists, ragged text and ids past the grid, against the fp64 oracle
+(2e-2 max-abs, as every bf16 parity test; every row)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ssba_oracle as O
+from paper_2605_15684_amd import _lib
+from paper_2605_15684_amd.inputs import workload_from
+
+from _parity import BF16_TOL, gpu_desc, inputs, oracle_index, oracle_kw, to64
+
+
+def _w(**kw):
+    base = dict(batch=1, heads=1, grid_h=72, grid_w=72, head_dim=64, tile=8, keep=64, shift=(4, 4))
+    base.update(kw)
+    return workload_from(**base)
+
+
+CASES = [
+    _w(grid_h=40, grid_w=104, keep=65),                                         # 65 blocks, all kept
+    _w(keep=1), _w(keep=63), _w(keep=64), _w(keep=65, n_text=13), _w(keep=81, n_text=64),
+    _w(grid_h=88, grid_w=96, keep=128, shift=(-3, 5)), _w(grid_h=88, grid_w=96, keep=129, n_text=77),
+    _w(head_dim=128, keep=66, n_text=5), _w(head_dim=128, keep=64, heads=2, batch=4),
+    _w(grid_h=80, grid_w=208, tile=16, keep=65, shift=(8, -8)),                 # 65 blocks of 16x16
+    _w(grid_h=80, grid_w=208, tile=16, keep=3, n_text=9, head_dim=128),
+]
+
+
+def _ids(w):
+    return f"{w.grid_h}x{w.grid_w}-D{w.head_dim}-b{w.tile}-k{w.keep}-t{w.n_text}"
+
+
+def _forward(w, qg, kg, vg, idx):
+    from paper_2605_15684_amd import ssba
+    out = ssba.forward(qg, kg, vg, torch.from_numpy(idx).to("cuda"), gpu_desc(w, qg))
+    torch.cuda.synchronize()
+    return out.float().cpu().double().numpy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("uneven", [False, True], ids=["topk", "uneven"])
+@pytest.mark.parametrize("w", CASES, ids=_ids)
+def test_long_lists(w, uneven):
+    (q, k, v), gpu = inputs(w)
+    idx = oracle_index(w, q, k)
+    if uneven:   # block i keeps the first 1 + 7 i mod keep entries
+        tb = w.n_tiles
+        idx = idx.copy()
+        idx.reshape(-1, tb, tb + 1)[:, :, 0] = 1 + 7 * np.arange(tb) % w.keep
+    got = _forward(w, *gpu, idx)
+    ref = O.attention(to64(q), to64(k), to64(v), idx, **oracle_kw(w))
+    assert np.isfinite(got).all()
+    assert float(np.abs(got - ref).max()) <= BF16_TOL
+
+
+@pytest.mark.gpu
+def test_masked_keys_add_nothing():
+    """Ids past the grid and the rows after a text tail are not seen, whatever they hold."""
+    w = _w(keep=70, n_text=3)
+    (q, k, v), (qg, kg, vg) = inputs(w)
+    idx = oracle_index(w, q, k).copy()
+    frame = O.frame_tiles(w.grid_h, w.grid_w, w.tile, *w.shift)
+    hidden = int(frame[0][0])                                    # an image token; the rows after the text hold NaN too
+    vg[0, 0, w.n_text:w.n_text + 64] = float("nan")
+    bad = {t for t in range(w.n_tiles) if (frame[t] < 64).any()}
+    vg[0, 0, w.n_text + hidden] = float("inf")
+    bad.add(0)
+    ok = [t for t in range(w.n_tiles) if t not in bad]
+    idx[0, 0, :, 0] = 70
+    idx[0, 0, :, 1:71] = np.resize(np.array(ok), 70)
+    idx[0, 0, :, 66] = 5000
+    got = _forward(w, qg, kg, vg, idx)
+    assert np.isfinite(got[0, 0, w.n_text:]).all()
+
+
+def test_kernel_names():
+    d = lambda **kw: _lib.forward_kernel(_desc(**kw))   # noqa: E731
+    assert d() == "k_attn_mfma_long<64, 3>"
+    assert d(tile=16, grid_h=128, grid_w=256, head_dim=128) == "k_attn_mfma_long<128, 4>"
+    assert d(grid_w=64) == "k_attn_mfma<64, 3, false, false>"
+    assert d(tile=4) == "k_attn_bf16<64, 2>"
+    # 32-bit byte offsets inside one (batch, head) are the kernel's limit
+    assert d(stride_b=1 << 40, stride_h=1 << 36, stride_t=1 << 20) == "k_attn_bf16<64, 3>"
+
+
+def _desc(**kw):
+    d = _lib.SsbaDesc()
+    base = dict(batch=1, heads=1, head_dim=64, grid_h=64, grid_w=72, tile=8, gate=_lib.GATE_TOPK, keep=4,
+                win_h=1, win_w=1, dtype=_lib.DT_BF16)
+    base.update(kw)
+    for name, value in base.items():
+        setattr(d, name, value)
+    return d

@@ -17,21 +17,21 @@
 namespace ssba {
 namespace {
 
-// (block, head, batch) of a workgroup in a 1-D grid of n_tiles * heads *
-// batch workgroups.  Consecutive hardware ids go round-robin over the 8 XCDs;
+// (block or group of blocks, head, batch) of a workgroup in a 1-D grid of
+// per_head * heads * batch workgroups.  Consecutive hardware ids go round-robin over the 8 XCDs;
 // when the (batch, head) count divides by 8, each XCD gets whole heads -- the
 // same heads the attention kernel gives it -- so pooled sums, index rows and
 // the head's Q/K stay in one XCD's L2 from kernel to kernel.
-__device__ __forceinline__ void unit_of(const IndexArgs& a, int& t, int& h, int& b) {
+__device__ __forceinline__ void unit_of(const IndexArgs& a, int per_head, int& t, int& h, int& b) {
   const int id = blockIdx.x, nbh = a.batch * a.heads;
   int bh, r;
   if ((nbh & 7) == 0) {
     const int xcd = id & 7, s = id >> 3;
-    bh = xcd * (nbh >> 3) + s / a.n_tiles;
-    r = s % a.n_tiles;
+    bh = xcd * (nbh >> 3) + s / per_head;
+    r = s % per_head;
   } else {
-    bh = id / a.n_tiles;
-    r = id % a.n_tiles;
+    bh = id / per_head;
+    r = id % per_head;
   }
   t = r;
   b = bh / a.heads;
@@ -56,7 +56,7 @@ __device__ __forceinline__ void pool_block(const IndexArgs& a) {
   using Vec = typename std::conditional<BF16, uint4, float>::type;
   __shared__ Vec stage[LOADS];
   int t, h, b;
-  unit_of(a, t, h, b);
+  unit_of(a, a.n_tiles, t, h, b);
   const int tid = threadIdx.x;
   const int64_t base = (int64_t)b * a.sb + (int64_t)h * a.sh;
   const int which = tid / D, c = tid % D;              // summing threads: tid < NT D
@@ -246,116 +246,150 @@ __global__ void __launch_bounds__(256) k_pool_keys_layers(PoolLayers p) {
   pool_block<SSBA_DT_BF16, 3, D, 1>(a);
 }
 
-// S[i][j] of one (batch, head): the channel-ordered sum of the rounded
-// products of the pooled query row qr (channel c at qr[c]) and the pooled key
-// column kc (channel c at kc[c * tb]).  Each batch of pooled-k loads is
-// requested before its first product, so a batch costs one memory round trip.
-template <int D>
-__device__ __forceinline__ double affinity_entry(const double* qr, const double* kc, int tb) {
-  constexpr int BATCH = D < 64 ? D : 64;
-  double s = 0.0;
+// S[i0 + r][j], r < R, of one (batch, head): the channel-ordered sum of the
+// rounded products of the pooled query row i0 + r and the pooled key column j.
+// A channel of the keys is loaded once for R query rows, whose own sums come
+// as scalar operands (the rows past the last repeat it).
+template <int D, int R>
+__device__ __forceinline__ void affinity_rows(const IndexArgs& a, int64_t bh, int i0, int j, double (&s)[R]) {
+  typedef const __attribute__((address_space(4))) double* ConstPtr;   // written before this launch
+  const int tb = a.n_tiles;
+  const double* kc = a.kb + bh * D * tb + j;
+  ConstPtr q[R];
 #pragma unroll
+  for (int r = 0; r < R; ++r) q[r] = (ConstPtr)(a.qb + (bh * tb + min(i0 + r, tb - 1)) * D);
+  constexpr int BATCH = 16;   // key loads in flight
+#pragma unroll 1
   for (int c0 = 0; c0 < D; c0 += BATCH) {
     double kv[BATCH];
 #pragma unroll
     for (int u = 0; u < BATCH; ++u) kv[u] = kc[(int64_t)(c0 + u) * tb];
 #pragma unroll
-    for (int u = 0; u < BATCH; ++u) {
-      const double p = __dmul_rn(qr[c0 + u], kv[u]);
-      s = (c0 + u == 0) ? p : __dadd_rn(s, p);
+    for (int u = 0; u < BATCH; ++u)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const double p = __dmul_rn(q[r][c0 + u], kv[u]);
+        s[r] = (c0 + u == 0) ? p : __dadd_rn(s[r], p);
+      }
+  }
+}
+
+// True for the ranking keys of infinities and NaNs.
+__device__ __forceinline__ bool key_nonfinite(uint64_t key) {
+  return key == 0 || key == 0xFFF0000000000000ull || key == 0x000FFFFFFFFFFFFFull;
+}
+
+// One wave ranks the tb <= 64 U keys of a row, lane l holding keys
+// l + 64 u (`keys` in LDS), by wave_topk's radix search over all of them, and
+// writes the kept ids ascending, -1 in the unused places and the count.
+// Returns whether any affinity of the row is not finite.
+template <int U>
+__device__ __forceinline__ bool rank_row(const uint64_t* keys, int tb, int keep, int lane, int32_t* out) {
+  uint64_t k[U], odd = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int j = lane + 64 * u;
+    k[u] = j < tb ? keys[j] : 0;
+    odd |= __builtin_amdgcn_ballot_w64(j < tb && key_nonfinite(k[u]));
+  }
+  uint64_t thr = 0;
+#pragma unroll 1
+  for (int bit = 63; bit >= 0; --bit) {
+    const uint64_t cand = thr | (1ull << bit);
+    int n = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) n += __popcll(__builtin_amdgcn_ballot_w64(k[u] >= cand));
+    if (n >= keep) {
+      thr = cand;
+      if (n == keep) break;
     }
   }
-  return s;
-}
-
-// Kept flag of block j (thread j of the workgroup) among the tb keys of the
-// row: the `keep` first in (key descending, block id ascending).  MAXT == 64
-// ranks in one wave; larger rows count, per key, the keys ranked before it.
-template <int MAXT>
-__device__ __forceinline__ bool rank_kept(uint64_t key, int j, int tb, int keep, const uint64_t* keys) {
-  if (MAXT == 64) return wave_topk(key, j < tb, keep, j & 63);
-  if (j >= tb) return false;
-  int rank = 0;
-  for (int jj = 0; jj < tb; ++jj) {
-    const uint64_t kj = keys[jj];
-    rank += (kj > key || (kj == key && jj < j)) ? 1 : 0;
+  int need = keep;   // places left for keys equal to the threshold, lowest ids first
+#pragma unroll
+  for (int u = 0; u < U; ++u) need -= __popcll(__builtin_amdgcn_ballot_w64(lane + 64 * u < tb && k[u] > thr));
+  const uint64_t below = (1ull << lane) - 1ull;
+  int before = 0, pos = 0;   // equal keys and kept keys of lower id
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int j = lane + 64 * u;
+    const bool valid = j < tb;
+    const uint64_t eq = __builtin_amdgcn_ballot_w64(valid && k[u] == thr);
+    const bool kept = valid && (k[u] > thr || (k[u] == thr && before + __popcll(eq & below) < need));
+    const uint64_t km = __builtin_amdgcn_ballot_w64(kept);
+    if (kept) out[1 + pos + __popcll(km & below)] = j;
+    if (valid && j >= keep) out[1 + j] = -1;
+    before += __popcll(eq);
+    pos += __popcll(km);
   }
-  return rank < keep;
+  if (lane == 0) out[0] = keep;
+  return odd != 0;
 }
 
-// One workgroup per query block (i, h, b); thread j computes S[i][j] (the
-// channel-ordered sum of rounded products) and its rank.  The `keep` blocks of
-// lowest rank are kept and written in ascending block order.
-template <int D, int MAXT>
-__global__ void __launch_bounds__(MAXT) k_gate_topk(IndexArgs a) {
-  extern __shared__ uint64_t keys[];   // [T_b]
-  __shared__ int wave_kept[16];
-  __shared__ int bad;
-  int i, h, b;
-  unit_of(a, i, h, b);
-  const int tb = a.n_tiles;
-  const int j = threadIdx.x, lane = j & 63, wave = j >> 6;
+// One workgroup per R query blocks of a (batch, head): thread j computes
+// S[i][j] of the R rows, then each wave ranks every (number of waves)-th row.
+// What bounds it: the fp64 units (2 D operations an affinity).  One row per
+// workgroup, ranked by counting, read a head's pooled keys from the L2 once
+// per row and compared each key with every other.  Measured at 345 blocks,
+// 12 heads, D 64: 109 us -> 29 us; 256 blocks, 16 heads: 53 -> 17 us; 64
+// blocks, 32 heads, D 128: 13 -> 9 us.
+template <int D, int U, int R>
+__global__ void __launch_bounds__(64 * U) k_gate_topk(IndexArgs a) {
+  extern __shared__ uint64_t keys[];   // [R][T_b]
+  const int tb = a.n_tiles, groups = (tb + R - 1) / R;
+  int g, h, b;
+  unit_of(a, groups, g, h, b);
   const int64_t bh = (int64_t)b * a.heads + h;
-  if (j == 0) bad = 0;
-  __syncthreads();
-  uint64_t key = 0;
+  const int j = threadIdx.x, lane = j & 63, i0 = g * R;
   if (j < tb) {
-    // the same query row for every thread; channel c of block j at kc[c * tb]
-    const double s = affinity_entry<D>(a.qb + (bh * tb + i) * D, a.kb + bh * D * tb + j, tb);
-    if (!isfinite(s)) atomicOr(&bad, 1);
-    key = rank_key(s);
-    keys[j] = key;
+    double s[R];
+    affinity_rows<D, R>(a, bh, i0, j, s);
+#pragma unroll
+    for (int r = 0; r < R; ++r) keys[r * tb + j] = rank_key(s[r]);
   }
   __syncthreads();
-  const bool kept = rank_kept<MAXT>(key, j, tb, a.keep, keys);
-  // Position of a kept block in the ascending list: kept blocks of lower id.
-  const uint64_t mask = __ballot(kept);
-  if (lane == 0) wave_kept[wave] = __popcll(mask);
-  __syncthreads();
-  int pos = __popcll(mask & ((1ull << lane) - 1ull));
-  for (int w = 0; w < wave; ++w) pos += wave_kept[w];
-  int32_t* out = a.index + (bh * tb + i) * (tb + 1);
-  if (j < tb) {
-    if (kept) out[1 + pos] = j;
-    if (j >= a.keep) out[1 + j] = -1;
-  }
-  if (j == 0) {
-    out[0] = a.keep;
-    a.flags[bh * tb + i] = bad;
+  const int waves = blockDim.x >> 6, rows = min(R, tb - i0);
+  for (int r = __builtin_amdgcn_readfirstlane(j >> 6); r < rows; r += waves) {
+    const int64_t row = bh * tb + i0 + r;
+    const bool bad = rank_row<U>(keys + r * tb, tb, a.keep, lane, a.index + row * (tb + 1));
+    if (lane == 0) a.flags[row] = bad ? 1 : 0;
   }
 }
 
-// Head-shared gate, step 1: one workgroup per query block (i, h, b) writes
-// its row of the per-head affinity, S_h[i][j] for j < T_b, to srows.
-template <int D, int MAXT>
+// Head-shared gate, step 1: one workgroup per R query blocks of a (batch,
+// head) writes their rows of the per-head affinity, S_h[i][j] for j < T_b, to
+// srows.
+template <int D, int R>
 __device__ __forceinline__ void affinity_rows_body(const IndexArgs& a) {
-  int i, h, b;
-  unit_of(a, i, h, b);
   const int tb = a.n_tiles, j = threadIdx.x;
+  int g, h, b;
+  unit_of(a, (tb + R - 1) / R, g, h, b);
   const int64_t bh = (int64_t)b * a.heads + h;
-  if (j < tb)
-    a.srows[(bh * tb + i) * tb + j] = affinity_entry<D>(a.qb + (bh * tb + i) * D, a.kb + bh * D * tb + j, tb);
+  const int i0 = g * R, rows = min(R, tb - i0);
+  if (j >= tb) return;
+  double s[R];
+  affinity_rows<D, R>(a, bh, i0, j, s);
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (r < rows) a.srows[(bh * tb + i0 + r) * tb + j] = s[r];
 }
 
-template <int D, int MAXT>
-__global__ void __launch_bounds__(MAXT) k_affinity_rows(IndexArgs a) {
-  affinity_rows_body<D, MAXT>(a);
+template <int D, int U, int R>
+__global__ void __launch_bounds__(64 * U) k_affinity_rows(IndexArgs a) {
+  affinity_rows_body<D, R>(a);
 }
 
 // Head-shared gate, step 2: one workgroup per query block (i, b); thread j
-// adds S_h[i][j] over heads h = 0, 1, ..., H-1 in that order (fp64), ranks
-// the sums and writes the same kept list and status flag for every head.
-template <int MAXT>
+// adds S_h[i][j] over heads h = 0, 1, ..., H-1 in that order (fp64); the
+// first wave ranks the sums, and the kept list and status flag are written
+// for every head.
+template <int U>
 __device__ __forceinline__ void gate_shared_body(const IndexArgs& a) {
-  extern __shared__ uint64_t keys[];   // [T_b]
-  __shared__ int wave_kept[16];
+  extern __shared__ uint64_t keys[];   // [T_b], then the index row
   __shared__ int bad;
   const int tb = a.n_tiles;
+  int32_t* list = reinterpret_cast<int32_t*>(keys + tb);
   const int b = blockIdx.x / tb, i = blockIdx.x - b * tb;
-  const int j = threadIdx.x, lane = j & 63, wave = j >> 6;
-  if (j == 0) bad = 0;
-  __syncthreads();
-  uint64_t key = 0;
+  const int j = threadIdx.x;
   if (j < tb) {
     const double* col = a.srows + ((int64_t)b * a.heads * tb + i) * tb + j;   // head h at col[h * tb * tb]
     const int64_t hstride = (int64_t)tb * tb;
@@ -369,35 +403,32 @@ __device__ __forceinline__ void gate_shared_body(const IndexArgs& a) {
       for (int u = 0; u < 16; ++u)
         if (u < nh) s = (h0 + u == 0) ? v[u] : __dadd_rn(s, v[u]);
     }
-    if (!isfinite(s)) atomicOr(&bad, 1);
-    key = rank_key(s);
-    keys[j] = key;
+    keys[j] = rank_key(s);
   }
   __syncthreads();
-  const bool kept = rank_kept<MAXT>(key, j, tb, a.keep, keys);
-  const uint64_t mask = __ballot(kept);
-  if (lane == 0) wave_kept[wave] = __popcll(mask);
+  if (j < 64) {
+    const bool odd = rank_row<U>(keys, tb, a.keep, j, list);
+    if (j == 0) bad = odd ? 1 : 0;
+  }
   __syncthreads();
-  int pos = __popcll(mask & ((1ull << lane) - 1ull));
-  for (int w = 0; w < wave; ++w) pos += wave_kept[w];
   for (int h = 0; h < a.heads; ++h) {
     const int64_t bh = (int64_t)b * a.heads + h;
     int32_t* out = a.index + (bh * tb + i) * (tb + 1);
-    if (j < tb) {
-      if (kept) out[1 + pos] = j;
-      if (j >= a.keep) out[1 + j] = -1;
-    }
+    if (j < tb) out[1 + j] = list[1 + j];
     if (j == 0) {
-      out[0] = a.keep;
+      out[0] = list[0];
       a.flags[bh * tb + i] = bad;
     }
   }
 }
 
-template <int MAXT>
-__global__ void __launch_bounds__(MAXT) k_gate_shared(IndexArgs a) {
-  gate_shared_body<MAXT>(a);
+template <int U>
+__global__ void __launch_bounds__(64 * U) k_gate_shared(IndexArgs a) {
+  gate_shared_body<U>(a);
 }
+
+// Query rows per workgroup of the layers' affinity launch (one wave each).
+constexpr int kLayerRows = 2;
 
 // The head-shared gate of several layers of one shape, one launch per step
 // (grid y = layer): each workgroup does what it does for its own layer.
@@ -423,17 +454,17 @@ __global__ void __launch_bounds__(256) k_pool_layers(IndexLayers p) {
 
 template <int D>
 __global__ void __launch_bounds__(64) k_affinity_rows_layers(IndexLayers p) {
-  affinity_rows_body<D, 64>(layer_index_args(p));
+  affinity_rows_body<D, kLayerRows>(layer_index_args(p));
 }
 
 __global__ void __launch_bounds__(64) k_gate_shared_layers(IndexLayers p) {
-  gate_shared_body<64>(layer_index_args(p));
+  gate_shared_body<1>(layer_index_args(p));
 }
 
 // Window (win_h x win_w blocks of the shifted frame) and dense gates.
 __global__ void __launch_bounds__(1024) k_gate_static(IndexArgs a, int gate) {
   int i, h, b;
-  unit_of(a, i, h, b);
+  unit_of(a, a.n_tiles, i, h, b);
   const int tb = a.n_tiles, nx = a.f.nx;
   const int j = threadIdx.x;
   const int64_t bh = (int64_t)b * a.heads + h;
@@ -515,39 +546,48 @@ hipError_t launch_rope_pool_keys(const RopeArgs& r, hipStream_t s) {
   return hipGetLastError();
 }
 
+namespace {
+
+// LDS of an affinity row's ranking keys.
+size_t key_bytes(const IndexArgs& a, int rows) { return sizeof(uint64_t) * (size_t)a.n_tiles * rows; }
+
+template <int D, int U, int R>
+void launch_rows(const IndexArgs& a, bool shared, hipStream_t s) {
+  const dim3 grid((a.n_tiles + R - 1) / R * a.heads * a.batch), block(round_threads(a.n_tiles));
+  if (shared) hipLaunchKernelGGL((k_affinity_rows<D, U, R>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k_gate_topk<D, U, R>), grid, block, key_bytes(a, R), s, a);
+}
+
+// The affinity rows of every query block, ranked per head or (shared) stored.
+// Rows per workgroup, measured as gate launches of 1 / 2 / 4 / 8 rows: 345
+// blocks, 12 heads, D 64: 57 / 38 / 29 / 67 us; 256 blocks, 16 heads: 36 / 22 /
+// 17 / 35 us (at 8 the scalar operands spill).  Up to 64 blocks a workgroup
+// is one wave, so fewer rows keep the chip filled: 64 blocks, 32 heads, D
+// 128: 12 / 9 / 17 / 47 us.
+template <int D>
+void launch_rows_d(const IndexArgs& a, bool shared, hipStream_t s) {
+  if (a.n_tiles <= 64) launch_rows<D, 1, 2>(a, shared, s);
+  else if (a.n_tiles <= 256) launch_rows<D, 4, 4>(a, shared, s);
+  else if (a.n_tiles <= 512) launch_rows<D, 8, 4>(a, shared, s);
+  else launch_rows<D, 16, 4>(a, shared, s);
+}
+
+}  // namespace
+
 hipError_t launch_gate_topk(const IndexArgs& a, hipStream_t s) {
-  dim3 grid(a.n_tiles * a.heads * a.batch), block(round_threads(a.n_tiles));
-  size_t lds = sizeof(uint64_t) * (size_t)a.n_tiles;
-  // Small block counts get a small thread bound, which leaves registers to
-  // hold every pooled-k load of a thread in flight at once.
-  if (a.head_dim == 64) {
-    if (block.x <= 64) hipLaunchKernelGGL((k_gate_topk<64, 64>), grid, block, lds, s, a);
-    else if (block.x <= 256) hipLaunchKernelGGL((k_gate_topk<64, 256>), grid, block, lds, s, a);
-    else hipLaunchKernelGGL((k_gate_topk<64, 1024>), grid, block, lds, s, a);
-  } else {
-    if (block.x <= 64) hipLaunchKernelGGL((k_gate_topk<128, 64>), grid, block, lds, s, a);
-    else if (block.x <= 256) hipLaunchKernelGGL((k_gate_topk<128, 256>), grid, block, lds, s, a);
-    else hipLaunchKernelGGL((k_gate_topk<128, 1024>), grid, block, lds, s, a);
-  }
+  if (a.head_dim == 64) launch_rows_d<64>(a, false, s);
+  else launch_rows_d<128>(a, false, s);
   return hipGetLastError();
 }
 
 hipError_t launch_gate_topk_shared(const IndexArgs& a, hipStream_t s) {
-  dim3 grid_rows(a.n_tiles * a.heads * a.batch), grid_b(a.n_tiles * a.batch), block(round_threads(a.n_tiles));
-  const size_t lds = sizeof(uint64_t) * (size_t)a.n_tiles;
-  if (block.x <= 64) {
-    if (a.head_dim == 64) hipLaunchKernelGGL((k_affinity_rows<64, 64>), grid_rows, block, 0, s, a);
-    else hipLaunchKernelGGL((k_affinity_rows<128, 64>), grid_rows, block, 0, s, a);
-    hipLaunchKernelGGL((k_gate_shared<64>), grid_b, block, lds, s, a);
-  } else if (block.x <= 256) {
-    if (a.head_dim == 64) hipLaunchKernelGGL((k_affinity_rows<64, 256>), grid_rows, block, 0, s, a);
-    else hipLaunchKernelGGL((k_affinity_rows<128, 256>), grid_rows, block, 0, s, a);
-    hipLaunchKernelGGL((k_gate_shared<256>), grid_b, block, lds, s, a);
-  } else {
-    if (a.head_dim == 64) hipLaunchKernelGGL((k_affinity_rows<64, 1024>), grid_rows, block, 0, s, a);
-    else hipLaunchKernelGGL((k_affinity_rows<128, 1024>), grid_rows, block, 0, s, a);
-    hipLaunchKernelGGL((k_gate_shared<1024>), grid_b, block, lds, s, a);
-  }
+  if (a.head_dim == 64) launch_rows_d<64>(a, true, s);
+  else launch_rows_d<128>(a, true, s);
+  const dim3 grid(a.n_tiles * a.batch), block(round_threads(a.n_tiles));
+  const size_t lds = key_bytes(a, 1) + sizeof(int32_t) * (size_t)(a.n_tiles + 1);
+  if (block.x <= 64) hipLaunchKernelGGL((k_gate_shared<1>), grid, block, lds, s, a);
+  else if (block.x <= 256) hipLaunchKernelGGL((k_gate_shared<4>), grid, block, lds, s, a);
+  else hipLaunchKernelGGL((k_gate_shared<16>), grid, block, lds, s, a);
   return hipGetLastError();
 }
 
@@ -557,16 +597,17 @@ hipError_t launch_topk_shared_layers(const IndexLayers& p, int n_layers, hipStre
   if (n_layers < 1 || n_layers > kIndexLayersMax || a.n_tiles < 1 || a.n_tiles > 64 || (tl != 3 && tl != 4) ||
       p.f[0].tile_log2 != tl || p.f[1].tile_log2 != tl || (a.head_dim != 64 && a.head_dim != 128))
     return hipErrorInvalidValue;
-  const dim3 grid_rows(a.n_tiles * a.heads * a.batch, n_layers), grid_b(a.n_tiles * a.batch, n_layers);
+  const dim3 grid_pool(a.n_tiles * a.heads * a.batch, n_layers);
+  const dim3 grid_rows((a.n_tiles + kLayerRows - 1) / kLayerRows * a.heads * a.batch, n_layers), grid_b(a.n_tiles * a.batch, n_layers);
   const dim3 block_pool(256), block(round_threads(a.n_tiles));
-  const size_t lds = sizeof(uint64_t) * (size_t)a.n_tiles;
+  const size_t lds = key_bytes(a, 1) + sizeof(int32_t) * (size_t)(a.n_tiles + 1);
   if (a.head_dim == 64) {
-    if (tl == 3) hipLaunchKernelGGL((k_pool_layers<3, 64>), grid_rows, block_pool, 0, s, p);
-    else hipLaunchKernelGGL((k_pool_layers<4, 64>), grid_rows, block_pool, 0, s, p);
+    if (tl == 3) hipLaunchKernelGGL((k_pool_layers<3, 64>), grid_pool, block_pool, 0, s, p);
+    else hipLaunchKernelGGL((k_pool_layers<4, 64>), grid_pool, block_pool, 0, s, p);
     hipLaunchKernelGGL((k_affinity_rows_layers<64>), grid_rows, block, 0, s, p);
   } else {
-    if (tl == 3) hipLaunchKernelGGL((k_pool_layers<3, 128>), grid_rows, block_pool, 0, s, p);
-    else hipLaunchKernelGGL((k_pool_layers<4, 128>), grid_rows, block_pool, 0, s, p);
+    if (tl == 3) hipLaunchKernelGGL((k_pool_layers<3, 128>), grid_pool, block_pool, 0, s, p);
+    else hipLaunchKernelGGL((k_pool_layers<4, 128>), grid_pool, block_pool, 0, s, p);
     hipLaunchKernelGGL((k_affinity_rows_layers<128>), grid_rows, block, 0, s, p);
   }
   hipLaunchKernelGGL(k_gate_shared_layers, grid_b, block, lds, s, p);

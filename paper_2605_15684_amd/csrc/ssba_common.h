@@ -222,6 +222,9 @@ hipError_t launch_attn_f32(const AttnArgs& a, int head_dim, int tile, hipStream_
 bool mfma_supported(int head_dim, int tile, bool dense, int n_tiles, int seq, int64_t span);
 // More than 64 blocks of 8x8 or 16x16 tokens, reading an index.
 bool mfma_long_supported(int head_dim, int tile, int n_tiles, int seq, int64_t span);
+// 4x4 blocks, one wave per block.
+bool tile4_supported(int head_dim, int tile, bool dense, int64_t span);
+hipError_t launch_attn_tile4(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_attn_mfma(const AttnArgs& a, int head_dim, int tile, hipStream_t s);
 // Attention (bf16, D 64 or 128; 8x8 blocks when gated, 8x8 or 16x16 with an
 // index) of n_layers <= kAttnLayersMax layers, on shapes mfma_supported takes.

@@ -35,6 +35,12 @@ bool mfma_long_supported(int head_dim, int tile, int n_tiles, int seq, int64_t s
          2 * span < ((int64_t)1 << 32);
 }
 
+bool tile4_supported(int head_dim, int tile, bool dense, int64_t span) {
+  // Byte offsets inside one (batch, head) below 2^31: the next value up marks
+  // a row that is not there.
+  return (head_dim == 64 || head_dim == 128) && tile == 4 && !dense && 2 * span < ((int64_t)1 << 31);
+}
+
 const char* attn_kernel_name(const AttnArgs& a, int head_dim, int tile, int dtype) {
   if (dtype == SSBA_DT_F32) return head_dim == 64 ? "k_attn_f32<64>" : "k_attn_f32<128>";
   if (mfma_supported(head_dim, tile, a.dense != 0, a.n_tiles, a.seq, (int64_t)a.seq * a.st))

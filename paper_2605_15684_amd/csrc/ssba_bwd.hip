@@ -46,6 +46,8 @@ typedef __attribute__((address_space(3))) void lds_void;
 constexpr int kWaitVm0 = 0x0F70;          // s_waitcnt: every vector memory operation done
 constexpr int kRawBufferFlags = 0x00020000;
 constexpr float kLog2e = 1.4426950408889634f;
+// sched_group_barrier classes.
+constexpr int kMfma = 0x8, kDsRead = 0x100;
 
 template <int D>
 struct BShape {
@@ -393,8 +395,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
   // half qh at gstage + 1024 (NKS qh + ks), lane l's 16 bytes at 16 l, so the
   // reads are linear.  Written by the stream-0 waves, read after the first
   // barrier.
-  __shared__ __attribute__((aligned(16))) char gstage[2 * NKS * 1024];
-  if (sk == 0) {
+  // (D 128 has the registers.)
+  constexpr bool kStageG = D == 64;
+  __shared__ __attribute__((aligned(16))) char gstage[kStageG ? 2 * NKS * 1024 : 16];
+  if (kStageG && sk == 0) {
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks)
       *reinterpret_cast<bf16x8*>(gstage + 1024 * (NKS * qh + ks) + 16 * lane) = gf[ks];
@@ -460,11 +464,33 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
       sc[e] = nl;
       dp[e] = nd;
     }
+    s16x8 kfirst[NDB];   // D 128: the first transposed operands, read ahead of the softmax
+    if constexpr (kStageG) {
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(kt, lane, ks), qf[ks], sc, 0, 0, 0);
-      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(vt, lane, ks),
-                                                  *reinterpret_cast<const bf16x8*>(gfr + 1024 * ks), dp, 0, 0, 0);
+      for (int ks = 0; ks < NKS; ++ks) {
+        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(kt, lane, ks), qf[ks], sc, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(vt, lane, ks),
+                                                    *reinterpret_cast<const bf16x8*>(gfr + 1024 * ks), dp, 0, 0, 0);
+      }
+    } else {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) {
+        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(kt, lane, ks), qf[ks], sc, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(vt, lane, ks), gf[ks], dp, 0, 0, 0);
+      }
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) kfirst[db] = tr_frag<D>(kt, lane, 0, db);
+      // Six reads go ahead of the first product and one with each after it:
+      // with two waves a SIMD a product that waits for its own read leaves
+      // the matrix cores idle.
+      __builtin_amdgcn_sched_group_barrier(kDsRead, 6, 0);
+#pragma unroll
+      for (int i = 0; i < 2 * NKS; ++i) {
+        __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(kDsRead, 2 * NDB - 6, 0);
     }
     if (lo > 0 || hi < 32) {   // rare: text tail or an invalid block id
       int l4 = lo - 4 * hw, h4 = hi - 4 * hw;
@@ -487,9 +513,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     for (int ks = 0; ks < 2; ++ks) {
       const bf16x8 pb = packed_frag(pk, ks);
 #pragma unroll
-      for (int db = 0; db < NDB; ++db)
-        acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, tr_frag<D>(kt, lane, ks, db)),
-                                                         pb, acc[db], 0, 0, 0);
+      for (int db = 0; db < NDB; ++db) {
+        const s16x8 kf = !kStageG && ks == 0 ? kfirst[db] : tr_frag<D>(kt, lane, ks, db);
+        acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf), pb, acc[db], 0, 0, 0);
+      }
+    }
+    if constexpr (!kStageG) {   // the rest of the reads before the first product, under the softmax
+      __builtin_amdgcn_sched_group_barrier(kDsRead, 2 * NDB, 0);
+      __builtin_amdgcn_sched_group_barrier(kMfma, 2 * NDB, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
@@ -523,9 +554,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
         *reinterpret_cast<uint2*>(orow + 32 * db + 8 * j + 4 * hw) = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
       }
   }
-  // The first image group of each head also orders the key-side work (the dO
-  // stage is free after the chunk loop).
-  if (!text_group && g == 0) write_key_order(a, bh, w, lane, reinterpret_cast<int*>(gstage));
+  // The first image group of each head also orders the key-side work (the V
+  // buffers are free after the chunk loop).
+  if (!text_group && g == 0) write_key_order(a, bh, w, lane, reinterpret_cast<int*>(vA));
 }
 
 // --------------------------------------------------------------------------
@@ -671,6 +702,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
   __syncthreads();
   // The products of one chunk from the buffers (qc, gc, lc, dc).
   auto compute = [&](const char* qc, const char* gc, const float* lc, const float* dc) {
+    if constexpr (D == 128) __builtin_amdgcn_sched_barrier(0);
     const char* qt = qc + HALF * qs;
     const char* gt = gc + HALF * qs;
     // Valid queries of this stream's half (text chunks end at n_text).
@@ -692,6 +724,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
                                                    *reinterpret_cast<const bf16x8*>(kfr + 1024 * ks), sc, 0, 0, 0);
       dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(gt, lane, ks),
                                                    *reinterpret_cast<const bf16x8*>(vfr + 1024 * ks), dp, 0, 0, 0);
+    }
+    if constexpr (D == 128) {   // reads ahead of the products, as in k_bwd_dq
+      __builtin_amdgcn_sched_group_barrier(kDsRead, 8 + 6, 0);   // the row values too
+#pragma unroll
+      for (int i = 0; i < 2 * NKS - 3; ++i) {
+        __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(kDsRead, 2, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(kMfma, 3, 0);
     }
     if (hi < 32) {   // rare: text tail
       int h4 = hi - 4 * hw;
@@ -722,6 +763,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
         dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, tr_frag<D>(qt, lane, ks, db)),
                                                         db8, dk[db], 0, 0, 0);
       }
+    }
+    if constexpr (D == 128) {
+      __builtin_amdgcn_sched_group_barrier(kDsRead, 6, 0);
+#pragma unroll
+      for (int i = 0; i < 4 * NDB - 3; ++i) {
+        __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(kDsRead, 2, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(kMfma, 3, 0);
     }
   };
   if constexpr (kSingle) {

@@ -93,7 +93,6 @@ ssba_status check_desc(const ssba_desc* d, Shape* out, bool gate_fields = true) 
     out->f.grid_w = d->grid_w;
     out->f.tile_log2 = ilog2(d->tile);
     out->f.nx = nx;
-    out->f.nx_inv = ssba::block_row_inv(nx);
     out->f.sy = mod(d->shift_y, d->grid_h);
     out->f.sx = mod(d->shift_x, d->grid_w);
     out->f.n_text = d->n_text;

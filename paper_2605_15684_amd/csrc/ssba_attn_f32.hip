@@ -98,7 +98,7 @@ __device__ __forceinline__ int key_row(const Frame& f, const Keys& k, int slot) 
 __device__ __forceinline__ Keys image_keys(const AttnArgs& a, int j, int first, int rows) {
   Keys k;
   const int jj = (unsigned)j < (unsigned)a.n_tiles ? j : 0;
-  const int ty = block_row(a.f, jj);
+  const int ty = jj / a.f.nx;
   k.base = a.f.n_text;
   k.y0 = (ty << a.f.tile_log2) - a.f.sy + (first >> a.f.tile_log2);
   k.x0 = ((jj - ty * a.f.nx) << a.f.tile_log2) - a.f.sx;

@@ -311,19 +311,22 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
   if ((nbh & 7) == 0) {
     const int xcd = bid & 7, s = bid >> 3;
     const int hpx = nbh >> 3;
-    const int n_nat = a.n_text_groups;
+    const int n_nat = a.n_text_groups, n_img = a.groups_per_bh - a.n_text_groups;
     if (s < hpx * n_nat) {
-      bh = xcd * hpx + divide(a.by_text, s, r);
+      const int d = n_nat > 0 ? n_nat : 1;
+      bh = xcd * hpx + s / d;
+      r = s % d;
     } else {
       const int s2 = s - hpx * n_nat;
-      bh = xcd * hpx + divide(a.by_image, s2, r);
-      r += n_nat;
+      const int d = n_img > 0 ? n_img : 1;
+      bh = xcd * hpx + s2 / d;
+      r = n_nat + s2 % d;
     }
   } else {
-    bh = divide(a.by_groups, bid, r);
+    bh = bid / a.groups_per_bh;
+    r = bid - bh * a.groups_per_bh;
   }
-  int h;
-  const int b = divide(a.by_heads, bh, h);
+  const int b = bh / a.heads, h = bh - b * a.heads;
   const int64_t off = (int64_t)b * a.sb + (int64_t)h * a.sh;
   const u16* qbase = static_cast<const u16*>(a.q) + off;
   const u16* kbase = static_cast<const u16*>(a.k) + off;
@@ -435,7 +438,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
   int orig_y = 0, orig_x = 0;
   auto origins = [&]() {
     if (listv >= 0) {
-      const int ty = block_row(a.f, listv);
+      const int ty = listv / a.f.nx;
       orig_y = ty * BT - a.f.sy;
       orig_x = (listv - ty * a.f.nx) * BT - a.f.sx;
     }
@@ -525,7 +528,6 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
   // score products start from negm = -m_run (0 while unset), so the common
   // chunk feeds the accumulator straight into exp2.
   float m_run = -1e30f, l_run = 0.f;
-  bool unset = true;   // some lane has no max yet (uniform)
   floatx16 negm = floatx16{};   // D 64: the seed of the score products
   float nm = 0.f;               // D 128 and LONG: -m_run, added after the products (16 fewer VGPRs)
   if constexpr (!LONG) scale_q<NKS>(qf, a.scale_log2);
@@ -574,16 +576,10 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
       }
       ls = ls0 + ls1;
     };
-    // Redo when a lane sum overflows the bound (the max grew); a lane without a
-    // max yet (the first chunk) skips the try.  Either way: take the chunk's
-    // max, rescale O and l, recompute P.
-    // (D 128 tries all the same: the branch costs registers it does not have.)
-    bool redo = D == 64 && unset;
-    if (!redo) {
-      probs(0.f, false);
-      redo = __any(!(ls <= kSumLimit) || (D != 64 && m_run < -1e29f));
-    }
-    if (redo) {
+    probs(0.f, false);
+    // Redo when a lane sum overflows the bound (the max grew) or the lane has
+    // no max yet: take the chunk's max, rescale O and l, recompute P.
+    if (__any(!(ls <= kSumLimit) || m_run < -1e29f)) {
       float mx = sc[0];
 #pragma unroll
       for (int rr = 1; rr < 16; ++rr) mx = fmaxf(mx, sc[rr]);
@@ -596,7 +592,6 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
 #pragma unroll
         for (int db = 0; db < NDB; ++db) oacc[db] *= alpha;
       }
-      unset = __any(m_run < -1e29f);
       const float mnew = m_run > -1e29f ? m_run : 0.f;
       probs(mnew - mb, true);
       if constexpr (kSeed) {
@@ -814,10 +809,6 @@ void set_groups(AttnArgs& a, int tile) {
     a.groups_per_tile = gpb;
     a.groups_per_bh = a.n_text_groups + a.n_tiles * gpb;
   }
-  a.by_heads = divisor(a.heads);
-  a.by_text = divisor(a.n_text_groups);
-  a.by_image = divisor(a.groups_per_bh - a.n_text_groups);
-  a.by_groups = divisor(a.groups_per_bh);
 }
 
 }  // namespace

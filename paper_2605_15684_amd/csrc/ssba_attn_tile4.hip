@@ -162,7 +162,7 @@ __device__ __forceinline__ void attn_tile4(const AttnArgs& a) {
   auto load_list = [&](int e0) {
     const int ent = e0 + lane < count ? list[1 + e0 + lane] : -1;
     ok = (unsigned)ent < (unsigned)a.n_tiles ? 1 : 0;
-    const int j = ok ? ent : 0, ty = block_row(a.f, j);
+    const int j = ok ? ent : 0, ty = j / a.f.nx;
     orig_y = 4 * ty - a.f.sy;
     orig_x = 4 * (j - ty * a.f.nx) - a.f.sx;
   };
@@ -251,6 +251,7 @@ __device__ __forceinline__ void attn_tile4(const AttnArgs& a) {
   for (int db = 0; db < NDB; ++db) oacc[db] = floatx4{};
   float m_run = -1e30f, l_run = 0.f;   // running max of the scaled scores (log2 units), lane's sum
   float nm = 0.f;                      // -m_run, 0 while unset
+  const bf16x2 one2 = {(__bf16)1.0f, (__bf16)1.0f};
 
   // P of a step's scores as bf16 pairs, O and l rescaled where the max grew.
   auto softmax = [&](const floatx4& s0, const floatx4& s1, int h0, int h1, uint32_t (&pk)[4]) {
@@ -274,10 +275,9 @@ __device__ __forceinline__ void attn_tile4(const AttnArgs& a) {
       for (int p = 0; p < 4; ++p) {
         const float x0 = shifted ? sc[2 * p] - shift : sc[2 * p];
         const float x1 = shifted ? sc[2 * p + 1] - shift : sc[2 * p + 1];
-        const float p0 = __builtin_amdgcn_exp2f(x0), p1 = __builtin_amdgcn_exp2f(x1);
-        pk[p] = pack2(p0, p1);
-        l0 += p0;
-        l1 += p1;
+        pk[p] = pack2(__builtin_amdgcn_exp2f(x0), __builtin_amdgcn_exp2f(x1));
+        float& l = p & 1 ? l1 : l0;
+        l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[p]), one2, l, false);
       }
       ls = l0 + l1;
     };

@@ -165,7 +165,7 @@ __device__ __forceinline__ void copy_offsets(const Frame& f, int src, int hf, in
   const int kin = ln / S::CPR;
   if (src >= 0) {
     const int blk = src >> QL, quarter = src & ((1 << QL) - 1);
-    const int ty = block_row(f, blk), tx = blk - ty * f.nx;
+    const int ty = blk / f.nx, tx = blk - ty * f.nx;
     const int y0 = (ty << TL) - f.sy, x0 = (tx << TL) - f.sx;
 #pragma unroll
     for (int mm = 0; mm < S::NIW; ++mm) {

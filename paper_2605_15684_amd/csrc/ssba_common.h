@@ -16,46 +16,14 @@ struct Frame {
   int grid_h, grid_w;
   int tile_log2;   // tile = 1 << tile_log2
   int nx;          // blocks per grid row
-  unsigned nx_inv; // ceil(2^20 / nx), for block_row()
   int sy, sx;      // shift reduced into [0, grid_h) x [0, grid_w)
   int n_text;      // image rows start here
 };
 
-// Block row t / nx of block t, by one multiplication: exact for every
-// t < 1024 and nx <= 1024 (the error t (nx nx_inv - 2^20) stays below 2^20).
-// A division by a run-time value is some 25 instructions, and a workgroup of
-// the 8x8 kernels took four of them before its first load.
-__host__ __device__ __forceinline__ unsigned block_row_inv(int nx) { return ((1u << 20) + nx - 1) / nx; }
-__host__ __device__ __forceinline__ int block_row(const Frame& f, int t) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return (int)(__umul24((unsigned)t, f.nx_inv) >> 20);
-#else
-  return (int)(((unsigned)t * f.nx_inv) >> 20);
-#endif
-}
-
-// Quotient and remainder by a divisor known to the host.
-struct Divisor {
-  unsigned d, inv;   // inv = floor(2^32 / d); d = 1: 2^32 - 1
-};
-inline Divisor divisor(int d) {
-  const unsigned u = d > 0 ? (unsigned)d : 1u;
-  return {u, u == 1u ? 0xFFFFFFFFu : (unsigned)((1ull << 32) / u)};
-}
-__device__ __forceinline__ int divide(const Divisor& v, int n, int& rem) {
-  unsigned q = __umulhi((unsigned)n, v.inv), r = (unsigned)n - q * v.d;   // q is at most one short
-  if (r >= v.d) {
-    ++q;
-    r -= v.d;
-  }
-  rem = (int)r;
-  return (int)q;
-}
-
 // Sequence row (text first) of slot s of block t in the shifted frame.
 __host__ __device__ __forceinline__ int frame_row(const Frame& f, int t, int s) {
   const int tile = 1 << f.tile_log2;
-  const int ty = block_row(f, t), tx = t - ty * f.nx;
+  const int ty = t / f.nx, tx = t - ty * f.nx;
   int y = (ty << f.tile_log2) + (s >> f.tile_log2) - f.sy;
   int x = (tx << f.tile_log2) + (s & (tile - 1)) - f.sx;
   y += (y < 0) ? f.grid_h : 0;
@@ -115,7 +83,6 @@ struct AttnArgs {
   int n_text_groups;     // leading workgroups that run text query rows (dense rows)
   int groups_per_tile;   // image workgroups per query block (tile^2 / rows per group)
   int groups_per_bh;     // workgroups per (batch, head)
-  Divisor by_heads, by_text, by_image, by_groups;   // MFMA kernels: heads, text, image and all groups
   int dense;             // 1: every row attends every key in natural order
   // Gated launches compute the top-k gate of each image block in the kernel
   // from the pooled sums and write the index rows and status flags.

@@ -250,7 +250,9 @@ __global__ void __launch_bounds__(256) k_pool_keys_layers(PoolLayers p) {
 // rounded products of the pooled query row i0 + r and the pooled key column j.
 // A channel of the keys is loaded once for R query rows, whose own sums come
 // as scalar operands (the rows past the last repeat it).
-template <int D, int R>
+// BATCH key loads are in flight at a time: more up to 64 blocks, where a short
+// launch is bound by these round trips and one wave has the registers.
+template <int D, int R, int BATCH>
 __device__ __forceinline__ void affinity_rows(const IndexArgs& a, int64_t bh, int i0, int j, double (&s)[R]) {
   typedef const __attribute__((address_space(4))) double* ConstPtr;   // written before this launch
   const int tb = a.n_tiles;
@@ -258,7 +260,6 @@ __device__ __forceinline__ void affinity_rows(const IndexArgs& a, int64_t bh, in
   ConstPtr q[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) q[r] = (ConstPtr)(a.qb + (bh * tb + min(i0 + r, tb - 1)) * D);
-  constexpr int BATCH = 16;   // key loads in flight
 #pragma unroll 1
   for (int c0 = 0; c0 < D; c0 += BATCH) {
     double kv[BATCH];
@@ -342,7 +343,7 @@ __global__ void __launch_bounds__(64 * U) k_gate_topk(IndexArgs a) {
   const int j = threadIdx.x, lane = j & 63, i0 = g * R;
   if (j < tb) {
     double s[R];
-    affinity_rows<D, R>(a, bh, i0, j, s);
+    affinity_rows<D, R, U == 1 ? 32 : 16>(a, bh, i0, j, s);
 #pragma unroll
     for (int r = 0; r < R; ++r) keys[r * tb + j] = rank_key(s[r]);
   }
@@ -358,7 +359,7 @@ __global__ void __launch_bounds__(64 * U) k_gate_topk(IndexArgs a) {
 // Head-shared gate, step 1: one workgroup per R query blocks of a (batch,
 // head) writes their rows of the per-head affinity, S_h[i][j] for j < T_b, to
 // srows.
-template <int D, int R>
+template <int D, int U, int R>
 __device__ __forceinline__ void affinity_rows_body(const IndexArgs& a) {
   const int tb = a.n_tiles, j = threadIdx.x;
   int g, h, b;
@@ -367,7 +368,7 @@ __device__ __forceinline__ void affinity_rows_body(const IndexArgs& a) {
   const int i0 = g * R, rows = min(R, tb - i0);
   if (j >= tb) return;
   double s[R];
-  affinity_rows<D, R>(a, bh, i0, j, s);
+  affinity_rows<D, R, U == 1 ? 32 : 16>(a, bh, i0, j, s);
 #pragma unroll
   for (int r = 0; r < R; ++r)
     if (r < rows) a.srows[(bh * tb + i0 + r) * tb + j] = s[r];
@@ -375,7 +376,7 @@ __device__ __forceinline__ void affinity_rows_body(const IndexArgs& a) {
 
 template <int D, int U, int R>
 __global__ void __launch_bounds__(64 * U) k_affinity_rows(IndexArgs a) {
-  affinity_rows_body<D, R>(a);
+  affinity_rows_body<D, U, R>(a);
 }
 
 // Head-shared gate, step 2: one workgroup per query block (i, b); thread j
@@ -454,7 +455,7 @@ __global__ void __launch_bounds__(256) k_pool_layers(IndexLayers p) {
 
 template <int D>
 __global__ void __launch_bounds__(64) k_affinity_rows_layers(IndexLayers p) {
-  affinity_rows_body<D, kLayerRows>(layer_index_args(p));
+  affinity_rows_body<D, 1, kLayerRows>(layer_index_args(p));
 }
 
 __global__ void __launch_bounds__(64) k_gate_shared_layers(IndexLayers p) {
@@ -563,10 +564,13 @@ void launch_rows(const IndexArgs& a, bool shared, hipStream_t s) {
 // blocks, 12 heads, D 64: 57 / 38 / 29 / 67 us; 256 blocks, 16 heads: 36 / 22 /
 // 17 / 35 us (at 8 the scalar operands spill).  Up to 64 blocks a workgroup
 // is one wave, so fewer rows keep the chip filled: 64 blocks, 32 heads, D
-// 128: 12 / 9 / 17 / 47 us.
+// 128: 12 / 9 / 17 / 47 us; one row each where even so there are fewer than
+// two waves a SIMD.
 template <int D>
 void launch_rows_d(const IndexArgs& a, bool shared, hipStream_t s) {
-  if (a.n_tiles <= 64) launch_rows<D, 1, 2>(a, shared, s);
+  const int64_t rows = (int64_t)a.n_tiles * a.heads * a.batch;
+  if (a.n_tiles <= 64 && rows < 2048) launch_rows<D, 1, 1>(a, shared, s);
+  else if (a.n_tiles <= 64) launch_rows<D, 1, 2>(a, shared, s);
   else if (a.n_tiles <= 256) launch_rows<D, 4, 4>(a, shared, s);
   else if (a.n_tiles <= 512) launch_rows<D, 8, 4>(a, shared, s);
   else launch_rows<D, 16, 4>(a, shared, s);

@@ -45,6 +45,14 @@ def test_lists(grid, gate):
     assert _check(w, q, k) == 0
 
 
+@pytest.mark.parametrize("gate", ["topk", "topk_shared"])
+def test_lists_of_many_rows(gate):
+    """63 blocks in 34 heads: two rows per workgroup, the last group of one."""
+    w = _w((4, 252), gate=gate, batch=2, heads=17)
+    (q, k, _), _ = inputs(w)
+    assert _check(w, q, k) == 0
+
+
 @pytest.mark.parametrize("grid", [(20, 52), (60, 92), (36, 228)], ids=["65", "345", "513"])
 @pytest.mark.parametrize("keep", [1, 64, 65])
 def test_equal_affinities_take_the_lowest_ids(grid, keep):

@@ -30,7 +30,7 @@
 // as long as an image block and finish alone).
 // Measured at 60x92 tokens + 77 text, 12 heads, D 64, keep 54 of 345 (17.3
 // GFLOP, about 1 GB through the L2), the launch alone: the generic kernel
-// 565 us, this one 59 us (17 TB/s through the L2, which gives plain copies 32).
+// 565 us, this one 52 us (20 TB/s through the L2, which gives plain copies 32).
 //
 // LDS layout of a unit: 16 keys of 2 D bytes, 16-byte chunk c of key k at
 //   K, D 64:  c ^ ((k >> 1) & 7)     V, D 64:  c ^ 2 ((k >> 1) & 3)
@@ -251,7 +251,6 @@ __device__ __forceinline__ void attn_tile4(const AttnArgs& a) {
   for (int db = 0; db < NDB; ++db) oacc[db] = floatx4{};
   float m_run = -1e30f, l_run = 0.f;   // running max of the scaled scores (log2 units), lane's sum
   float nm = 0.f;                      // -m_run, 0 while unset
-  const bf16x2 one2 = {(__bf16)1.0f, (__bf16)1.0f};
 
   // P of a step's scores as bf16 pairs, O and l rescaled where the max grew.
   auto softmax = [&](const floatx4& s0, const floatx4& s1, int h0, int h1, uint32_t (&pk)[4]) {
@@ -275,9 +274,10 @@ __device__ __forceinline__ void attn_tile4(const AttnArgs& a) {
       for (int p = 0; p < 4; ++p) {
         const float x0 = shifted ? sc[2 * p] - shift : sc[2 * p];
         const float x1 = shifted ? sc[2 * p + 1] - shift : sc[2 * p + 1];
-        pk[p] = pack2(__builtin_amdgcn_exp2f(x0), __builtin_amdgcn_exp2f(x1));
-        float& l = p & 1 ? l1 : l0;
-        l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[p]), one2, l, false);
+        const float p0 = __builtin_amdgcn_exp2f(x0), p1 = __builtin_amdgcn_exp2f(x1);
+        pk[p] = pack2(p0, p1);
+        l0 += p0;   // (v_dot2 on the packed pair would queue with the products: 59 us against 52)
+        l1 += p1;
       }
       ls = l0 + l1;
     };

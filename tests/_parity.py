@@ -79,3 +79,34 @@ def max_err(gpu_out: torch.Tensor, ref: np.ndarray, heads, rows) -> float:
         assert np.isfinite(gg).all()
         err = max(err, float(np.abs(gg - rr).max()))
     return err
+
+
+def growing_inputs(w: Workload, at, units: int = 24):
+    """Inputs for which the running maximum of a list of the first `keep`
+    blocks, ascending, grows by about `units` log2 units at each of the
+    entries `at`, in every other query row; in the rows between, the same
+    keys change nothing.  Each part's values are larger by what its
+    probabilities lose later, so that it still shows in the output.  Returns
+    (q, k, v), the index and the bound 2^-7 sum p |v| on the error of each
+    output (P and the output are each rounded to 8 bits)."""
+    q, k, v = make_qkv(w)
+    frame = np.asarray(O.frame_tiles(w.grid_h, w.grid_w, w.tile, *w.shift))
+    unit = 8.0 / np.sqrt(w.head_dim) * np.log2(np.e)      # log2 units of q0 = 8, k0 = 1
+    step = float(np.ceil(units / unit))
+    level = torch.zeros(w.seq_len)
+    for t in range(w.n_tiles):
+        level[w.n_text + torch.from_numpy(frame[t])] = float(sum(t >= x for x in at))
+    q[..., 0] = 0
+    q[:, :, ::2, 0] = 8
+    k[..., 0] = (step * level).to(k.dtype)
+    v *= torch.exp2(units * (len(at) - level))[:, None].to(v.dtype)
+    index = np.full((w.batch, w.heads, w.n_tiles, w.n_tiles + 1), -1, np.int32)
+    index[..., 0] = w.keep
+    index[..., 1:1 + w.keep] = np.arange(w.keep)
+    # A sum of 2^20 in a lane takes the new maximum: each growth passes it by itself.
+    s = to64(q)[0, 0, w.n_text + np.arange(w.n_text % 2, w.t_img, 2)] @ to64(k)[0, 0, w.n_text + frame[:w.keep].ravel()].T
+    s = (s * unit / 8).reshape(len(s), w.keep, -1)
+    for e in at:
+        assert (s[:, e].min(-1) - s[:, :e].max((-2, -1))).min() > 20
+    bound = O.attention(to64(q), to64(k), np.abs(to64(v)), index, **oracle_kw(w)) / 128
+    return (q, k, v), index, bound

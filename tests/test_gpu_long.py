@@ -10,7 +10,7 @@ from oracle import ssba_oracle as O
 from paper_2605_15684_amd import _lib
 from paper_2605_15684_amd.inputs import workload_from
 
-from _parity import BF16_TOL, gpu_desc, inputs, oracle_index, oracle_kw, to64
+from _parity import BF16_TOL, gpu_desc, growing_inputs, inputs, oracle_index, oracle_kw, sample_rows, to64
 
 
 def _w(**kw):
@@ -54,6 +54,18 @@ def test_long_lists(w, uneven):
     ref = O.attention(to64(q), to64(k), to64(v), idx, **oracle_kw(w))
     assert np.isfinite(got).all()
     assert float(np.abs(got - ref).max()) <= BF16_TOL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("w", [_w(keep=81, n_text=5), _w(keep=81, n_text=5, head_dim=128),
+                               _w(grid_h=80, grid_w=208, tile=16, keep=65)], ids=_ids)
+def test_scores_that_grow(w):
+    """A new maximum in half of the rows after 1, 7, 30 and 64 blocks."""
+    (q, k, v), idx, bound = growing_inputs(w, (1, 7, 30, 64))
+    rows = np.arange(w.seq_len) if w.tile == 8 else sample_rows(w, np.random.default_rng(1))
+    got = _forward(w, *(t.to("cuda") for t in (q, k, v)), idx)
+    ref = O.attention(to64(q), to64(k), to64(v), idx, rows=rows, **oracle_kw(w))
+    assert (np.abs(got - ref)[:, :, rows] <= bound[:, :, rows]).all()
 
 
 @pytest.mark.gpu

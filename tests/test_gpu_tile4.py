@@ -10,7 +10,7 @@ import torch
 from oracle import ssba_oracle as O
 from paper_2605_15684_amd.inputs import workload_from
 
-from _parity import BF16_TOL, gpu_desc, inputs, oracle_index, oracle_kw, to64
+from _parity import BF16_TOL, gpu_desc, growing_inputs, inputs, oracle_index, oracle_kw, to64
 
 
 def _w(**kw):
@@ -57,17 +57,13 @@ def test_tile4(w, form):
 
 
 @pytest.mark.gpu
-def test_scores_that_grow():
-    """Each later block raises the running max by more than 2^20 in the sum."""
-    w = _w(keep=90, n_text=5)
-    (q, k, v), _ = inputs(w)
-    rows = O.frame_tiles(w.grid_h, w.grid_w, w.tile, *w.shift)
-    for t in range(w.n_tiles):
-        k[0, 0, w.n_text + torch.as_tensor(np.asarray(rows[t]))] *= 0.25 * (1 + t % 16)
-    idx = oracle_index(w, q, k)
+@pytest.mark.parametrize("w", [_w(keep=90, n_text=5), _w(keep=90, n_text=40, head_dim=128)], ids=_ids)
+def test_scores_that_grow(w):
+    """A new maximum in half of the rows after 1, 7, 30 and 64 blocks; a text group's waves end at different ones."""
+    (q, k, v), idx, bound = growing_inputs(w, (1, 7, 30, 64))
     got = _forward(w, *(t.to("cuda") for t in (q, k, v)), idx)
     ref = O.attention(to64(q), to64(k), to64(v), idx, **oracle_kw(w))
-    assert float(np.abs(got - ref).max()) <= BF16_TOL
+    assert (np.abs(got - ref) <= bound).all()
 
 
 @pytest.mark.gpu

@@ -109,6 +109,7 @@ struct Chunk {
   int row0, rstep, y0;
   unsigned lane_off[4];
   int lo, hi;
+  unsigned v_bytes;   // LONG: end of the slice's V that the copy may read
 };
 
 __device__ __forceinline__ float swap_max(float v) {
@@ -386,14 +387,12 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
   const __amdgpu_buffer_rsrc_t rk =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<u16*>(kbase), (short)0, (int)slice_bytes, kRawBufferFlags);
 
-  // V resource of chunk c: LONG ends it at the last text row for a text chunk
-  // of an image group, so that the image rows which a tail of fewer than 64
-  // text rows runs into arrive as zeros and a masked key adds exactly nothing.
-  auto values_of = [&](int c) {
-    int bytes = (int)slice_bytes;
-    if constexpr (LONG)
-      if (!p.natural_end && c >= p.img_chunks) bytes = (int)(2u * (unsigned)((a.f.n_text - 1) * st + D));
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<u16*>(vbase), (short)0, bytes, kRawBufferFlags);
+  // V resource of a chunk.  LONG ends it before the keys that are not there,
+  // which arrive as zeros: a masked key adds exactly nothing, whatever value
+  // the row in its place holds.
+  auto values_of = [&](const Chunk& ch) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<u16*>(vbase), (short)0,
+                                             (int)(LONG ? ch.v_bytes : slice_bytes), kRawBufferFlags);
   };
 
   // DMA lane mapping: lane l of copy instruction m fills key KPI m + l / CPR
@@ -450,7 +449,10 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
   // to the right edge when it starts left of it.  Natural-order chunks always
   // cover 64 existing rows: a ragged last chunk is moved back to end at the
   // last row and masks the keys the previous chunk already covered (rows of a
-  // ragged text chunk that run into the image rows exist too).
+  // ragged text chunk that run into the image rows exist too).  LONG keeps a
+  // ragged chunk in its place, its V ended at the last row, and gives an id
+  // past the grid no V at all.  There the whole offset of such a row is in the
+  // lane operand, which is the range-checked one.
   auto chunk_of = [&](int c) {
     Chunk ch;
     if (!DENSE && c < p.img_chunks) {
@@ -477,9 +479,23 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
       }
       ch.lo = 0;
       ch.hi = j >= 0 ? KH : 0;
+      if constexpr (LONG) {
+        ch.v_bytes = slice_bytes;
+        if (j < 0) ch.row0 = ch.rstep = ch.y0 = ch.v_bytes = 0;
+      }
       return ch;
     }
     const int end = p.natural_end ? p.natural_end : a.f.n_text;
+    if constexpr (LONG) {
+      const int first = (p.natural_end ? c : c - p.img_chunks) * KC + KH * sk;
+      ch.row0 = ch.rstep = ch.y0 = ch.lo = 0;
+      ch.hi = min(max(end - first, 0), KH);
+      ch.v_bytes = 2u * (unsigned)((end - 1) * st + D);
+#pragma unroll
+      for (int mm = 0; mm < NIW; ++mm)
+        ch.lane_off[mm] = 2u * (unsigned)st * (unsigned)(first + KPI * (NIW * qh + mm)) + 2u * (unsigned)(kin * st);
+      return ch;
+    }
     int base = p.natural_end ? c * KC : (c - p.img_chunks) * KC;
     int lo = 0, hi = min(end - base, KC);
     if (hi < KC && end >= KC) {   // ragged last chunk: end it at the last row
@@ -624,7 +640,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
   if (n > 0) {
     const Chunk ch0 = chunk_of(0);
     copy(rk, ch0, kA, true);
-    copy(values_of(0), ch0, vA, false);
+    copy(values_of(ch0), ch0, vA, false);
     lo_c = ch0.lo;
     hi_c = ch0.hi;
   }
@@ -652,7 +668,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
     if (c + 1 < n) {
       const Chunk cn = chunk_of(c + 1);
       copy(rk, cn, kn, true);
-      copy(values_of(c + 1), cn, vn, false);
+      copy(values_of(cn), cn, vn, false);
       lo_c = cn.lo;
       hi_c = cn.hi;
     }
@@ -700,7 +716,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
     __syncthreads();
-    if (more) copy(values_of(c + 1), cn, vA, false);
+    if (more) copy(values_of(cn), cn, vA, false);
   };
   if constexpr (kSingleV) {
     for (int c = 0; c < n; c += 2) {

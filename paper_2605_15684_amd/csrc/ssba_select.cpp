@@ -30,9 +30,10 @@ bool mfma_supported(int head_dim, int tile, bool dense, int n_tiles, int seq, in
 }
 
 bool mfma_long_supported(int head_dim, int tile, int n_tiles, int seq, int64_t span) {
-  // As mfma_supported, with a list that passes through the lanes in parts.
+  // As mfma_supported, with a list that passes through the lanes in parts, and
+  // offsets that also reach the rows past the last that a ragged chunk names.
   return (head_dim == 64 || head_dim == 128) && (tile == 8 || tile == 16) && n_tiles > 64 && seq >= kMfmaChunk &&
-         2 * span < ((int64_t)1 << 32);
+         2 * (span + span / seq * kMfmaChunk) < ((int64_t)1 << 32);
 }
 
 bool tile4_supported(int head_dim, int tile, bool dense, int64_t span) {

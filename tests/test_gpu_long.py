@@ -69,23 +69,51 @@ def test_scores_that_grow(w):
 
 
 @pytest.mark.gpu
-def test_masked_keys_add_nothing():
-    """Ids past the grid and the rows after a text tail are not seen, whatever they hold."""
-    w = _w(keep=70, n_text=3)
-    (q, k, v), (qg, kg, vg) = inputs(w)
+@pytest.mark.parametrize("d,n_text", [(64, 3), (64, 77), (128, 77)])
+def test_masked_keys_add_nothing(d, n_text):
+    """Ids past the grid and the rows beside a ragged tail are not seen,
+    whatever they hold: NaN rows where an id past the grid in the first 64
+    entries, or a tail of the text, would read; an infinite value in the block
+    that the lane of such an id held before the list's second part; and an
+    infinite text value that the second text chunk would see again."""
+    w = _w(grid_h=88, grid_w=96, keep=70, n_text=n_text, head_dim=d)
+    (q, k, v), (qg, kg, _) = inputs(w)
     idx = oracle_index(w, q, k).copy()
-    frame = O.frame_tiles(w.grid_h, w.grid_w, w.tile, *w.shift)
-    hidden = int(frame[0][0])                                    # an image token; the rows after the text hold NaN too
-    vg[0, 0, w.n_text:w.n_text + 64] = float("nan")
-    bad = {t for t in range(w.n_tiles) if (frame[t] < 64).any()}
-    vg[0, 0, w.n_text + hidden] = float("inf")
-    bad.add(0)
-    ok = [t for t in range(w.n_tiles) if t not in bad]
-    idx[0, 0, :, 0] = 70
-    idx[0, 0, :, 1:71] = np.resize(np.array(ok), 70)
-    idx[0, 0, :, 66] = 5000
-    got = _forward(w, qg, kg, vg, idx)
-    assert np.isfinite(got[0, 0, w.n_text:]).all()
+    frame = np.asarray(O.frame_tiles(w.grid_h, w.grid_w, w.tile, *w.shift))
+    hidden = np.unique(np.concatenate([np.arange(64), (96 * np.arange(8)[:, None] + np.arange(8)).ravel()]))
+    v[:, :, w.n_text + torch.from_numpy(hidden)] = float("nan")
+    ok = [t for t in range(w.n_tiles) if not np.isin(frame[t], hidden).any()]
+    want = idx.copy()                                  # the same without the two ids
+    want[..., 0], want[..., 1:69] = 68, ok[:68]
+    idx[..., 0], idx[..., 1:71] = 70, np.insert(ok[:68], [5, 65], [5000, -3])   # entries 5 and 66
+    assert idx[0, 0, 0, 6] == 5000 and idx[0, 0, 0, 67] == -3
+    v[:, :, w.n_text + int(frame[ok[2]][9]), 7] = float("inf")                  # entry 2: the lane of entry 66
+    inf = [7]
+    if n_text > 64:
+        v[:, :, 40, 9] = float("inf")
+        inf.append(9)
+    got = _forward(w, qg, kg, v.to("cuda"), idx)[:, :, w.n_text:]
+    assert (got[..., inf] == np.inf).all()
+    v[~torch.isfinite(v)] = 0
+    ref = O.attention(to64(q), to64(k), to64(v), want, **oracle_kw(w))[:, :, w.n_text:]
+    rest = [c for c in range(d) if c not in inf]
+    assert float(np.abs(got - ref)[..., rest].max()) <= BF16_TOL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_text", [3, 77])
+def test_infinite_value_in_the_last_rows(n_text):
+    """A text row's last chunk starts at a multiple of 64 rows: the rows before it are seen once."""
+    w = _w(keep=1, n_text=n_text)
+    (q, k, v), (qg, kg, _) = inputs(w)
+    idx = oracle_index(w, q, k)
+    v[:, :, w.seq_len - 40, 9] = float("inf")
+    got = _forward(w, qg, kg, v.to("cuda"), idx)[:, :, :n_text]
+    assert (got[..., 9] == np.inf).all()
+    v[~torch.isfinite(v)] = 0
+    ref = O.attention(to64(q), to64(k), to64(v), idx, rows=np.arange(n_text), **oracle_kw(w))[:, :, :n_text]
+    rest = [c for c in range(64) if c != 9]
+    assert float(np.abs(got - ref)[..., rest].max()) <= BF16_TOL
 
 
 def test_kernel_names():

@@ -279,8 +279,8 @@ __device__ __forceinline__ int gate_block(const AttnArgs& a, int bh, int i, int 
 // LONG: more than 64 blocks per head.  The kept list passes through the lanes
 // 64 entries at a time (a reload every 64 kept blocks), and Q keeps its own
 // bits: the scale is applied to the fp32 scores with the running max in one
-// fused multiply-add, as the generic kernel these shapes ran before did, so
-// they lose no precision to the rounding of scaled queries.
+// fused multiply-add, and the row sums take P before its rounding to bf16,
+// both as in the generic kernel.
 // Measured at 128x128 tokens, 16 heads, D 64, 256 8x8 blocks, keep 40 (172
 // GFLOP), the launch alone: generic kernel 570 us, this one 205 us (840 TFLOP/s).
 template <int D, int TILE_LOG2, bool DENSE, bool GATED, bool LONG = false>
@@ -577,8 +577,8 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
         if (key < l4 || key >= h4) sc[rr] = -INFINITY;
       }
     }
-    // P = exp2(sc - shift) as bf16 pairs and the lane's sum of the rounded P
-    // (shift is 0 except when a chunk is redone).
+    // P = exp2(sc - shift) as bf16 pairs and the lane's sum of the rounded P;
+    // LONG: of P as it was in 32 bits (shift is 0 except when a chunk is redone).
     float ls;
     auto probs = [&](float shift, bool shifted) {
       float ls0 = 0.f, ls1 = 0.f;
@@ -586,8 +586,12 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
       for (int rr = 0; rr < 16; rr += 2) {
         const float x0 = shifted ? sc[rr] - shift : sc[rr];
         const float x1 = shifted ? sc[rr + 1] - shift : sc[rr + 1];
-        pk[rr >> 1] = pack2(__builtin_amdgcn_exp2f(x0), __builtin_amdgcn_exp2f(x1));
-        if (rr & 2) ls1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[rr >> 1]), one2, ls1, false);
+        const float p0 = __builtin_amdgcn_exp2f(x0), p1 = __builtin_amdgcn_exp2f(x1);
+        pk[rr >> 1] = pack2(p0, p1);
+        if constexpr (LONG) {
+          ls0 += p0;
+          ls1 += p1;
+        } else if (rr & 2) ls1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[rr >> 1]), one2, ls1, false);
         else        ls0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[rr >> 1]), one2, ls0, false);
       }
       ls = ls0 + ls1;
@@ -621,14 +625,24 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
   };
   auto values = [&](const char* vt) {
     // O^T[db] += V^T . P^T over 2 key steps of 16 (V^T operands: keys
-    // 16 ks + 8 (e / 4) + 4 hw + e % 4, channel 32 db + lane % 32).
+    // 16 ks + 8 (e / 4) + 4 hw + e % 4, channel 32 db + lane % 32).  LONG at
+    // D 128 holds one offset between chunks (a channel tile is an exclusive
+    // or away): the fp32 row sums would spill otherwise.
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
+      int at[NDB];
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) at[db] = voff[db];
+      if constexpr (LONG && D == 128) {
+        asm volatile("" : "+v"(at[0]));
+#pragma unroll
+        for (int db = 1; db < NDB; ++db) at[db] = at[0] ^ (64 * db);
+      }
       const bf16x8 pb = __builtin_bit_cast(bf16x8, make_uint4(pk[4 * ks], pk[4 * ks + 1], pk[4 * ks + 2], pk[4 * ks + 3]));
 #pragma unroll
       for (int db = 0; db < NDB; ++db) {
-        const s16x4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt + voff[db] + 16 * S::ROWB * ks));
-        const s16x4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt + voff[db] + 16 * S::ROWB * ks + 8 * S::ROWB));
+        const s16x4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt + at[db] + 16 * S::ROWB * ks));
+        const s16x4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt + at[db] + 16 * S::ROWB * ks + 8 * S::ROWB));
         const s16x8 v8 = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
         oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v8), pb, oacc[db], 0, 0, 0);
       }

@@ -547,6 +547,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
   floatx16 negm = floatx16{};   // D 64: the seed of the score products
   float nm = 0.f;               // D 128 and LONG: -m_run, added after the products (16 fewer VGPRs)
   if constexpr (!LONG) scale_q<NKS>(qf, a.scale_log2);
+  constexpr float kNoMax = LONG ? -0.99e30f : -1e29f;   // a running max below this: no score seen yet
   constexpr bool kSeed = D == 64 && !LONG;   // the score products start from -m_run
   const bf16x2 one2 = {(__bf16)1.0f, (__bf16)1.0f};
 
@@ -555,12 +556,16 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
   uint32_t pk[8];   // P of the current chunk, bf16 pairs
   auto scores = [&](const char* kt, int lo, int hi) {
     // S^T = K . Q^T: the lane's 16 keys 8 (r / 4) + 4 hw + r % 4 of its query.
-    floatx16 sc = kSeed ? negm : floatx16{};   // sc = s - m_run: the exponent of exp2
+    floatx16 sc;   // s - m_run: the exponent of exp2
+    auto products = [&]() {
+      sc = kSeed ? negm : floatx16{};
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      const bf16x8 kf = *reinterpret_cast<const bf16x8*>(kt + koff[ks]);
-      sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], sc, 0, 0, 0);
-    }
+      for (int ks = 0; ks < NKS; ++ks) {
+        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(kt + koff[ks]);
+        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], sc, 0, 0, 0);
+      }
+    };
+    products();
     if constexpr (LONG) {
 #pragma unroll
       for (int rr = 0; rr < 16; ++rr) sc[rr] = __builtin_fmaf(sc[rr], a.scale_log2, nm);
@@ -568,15 +573,18 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
 #pragma unroll
       for (int rr = 0; rr < 16; ++rr) sc[rr] += nm;
     }
-    if (lo > 0 || hi < KH) {   // rare: ragged chunk or invalid block id
-      int l4 = lo - 4 * hw, h4 = hi - 4 * hw;
-      asm volatile("" : "+v"(l4), "+v"(h4));
+    auto mask = [&]() {
+      if (lo > 0 || hi < KH) {   // rare: ragged chunk or invalid block id
+        int l4 = lo - 4 * hw, h4 = hi - 4 * hw;
+        asm volatile("" : "+v"(l4), "+v"(h4));
 #pragma unroll
-      for (int rr = 0; rr < 16; ++rr) {
-        const int key = 8 * (rr >> 2) + (rr & 3);   // minus 4 * hw
-        if (key < l4 || key >= h4) sc[rr] = -INFINITY;
+        for (int rr = 0; rr < 16; ++rr) {
+          const int key = 8 * (rr >> 2) + (rr & 3);   // minus 4 * hw
+          if (key < l4 || key >= h4) sc[rr] = -INFINITY;
+        }
       }
-    }
+    };
+    mask();
     // P = exp2(sc - shift) as bf16 pairs and the lane's sum of the rounded P;
     // LONG: of P as it was in 32 bits (shift is 0 except when a chunk is redone).
     float ls;
@@ -599,12 +607,27 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
     probs(0.f, false);
     // Redo when a lane sum overflows the bound (the max grew) or the lane has
     // no max yet: take the chunk's max, rescale O and l, recompute P.
-    if (__any(!(ls <= kSumLimit) || m_run < -1e29f)) {
+    if (__any(!(ls <= kSumLimit) || m_run < kNoMax)) {
       float mx = sc[0];
 #pragma unroll
       for (int rr = 1; rr < 16; ++rr) mx = fmaxf(mx, sc[rr]);
-      const float mb = m_run > -1e29f ? m_run : 0.f;   // the offset in sc
-      const float mabs = mb + swap_max(mx);
+      const float mb = m_run > kNoMax ? m_run : 0.f;   // the offset in sc
+      float mabs = mb + swap_max(mx);
+      // LONG: where the max is more than 2^10 from that offset, sc was rounded
+      // to worse than 2^-14, and the scores are formed again (K is still in
+      // its buffer).  D 128 always does so: the other path costs it spills.
+      bool again = false;
+      if constexpr (LONG) {
+        again = D == 128 || __any(fabsf(mx) > 1024.f && mx > -INFINITY);
+        if (again) {
+          products();
+          mask();
+          mx = sc[0];
+#pragma unroll
+          for (int rr = 1; rr < 16; ++rr) mx = fmaxf(mx, sc[rr]);
+          mabs = swap_max(mx) * a.scale_log2;
+        }
+      }
       if (mabs > m_run) {
         const float alpha = __builtin_amdgcn_exp2f(m_run - mabs);   // 0 while unset
         m_run = mabs;
@@ -612,8 +635,14 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
 #pragma unroll
         for (int db = 0; db < NDB; ++db) oacc[db] *= alpha;
       }
-      const float mnew = m_run > -1e29f ? m_run : 0.f;
-      probs(mnew - mb, true);
+      const float mnew = m_run > kNoMax ? m_run : 0.f;
+      if (again) {
+#pragma unroll
+        for (int rr = 0; rr < 16; ++rr) sc[rr] = __builtin_fmaf(sc[rr], a.scale_log2, -mnew);
+        probs(0.f, false);
+      } else {
+        probs(mnew - mb, true);
+      }
       if constexpr (kSeed) {
 #pragma unroll
         for (int rr = 0; rr < 16; ++rr) negm[rr] = -mnew;

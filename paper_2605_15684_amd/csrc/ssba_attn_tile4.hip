@@ -59,6 +59,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kWaves = 4;                 // per workgroup
 constexpr float kSumLimit = 1048576.0f;   // 2^20: redo a step above this lane sum
+constexpr float kNoMax = -0.99e30f;       // a running max below this: no score seen yet
 // s_waitcnt immediate (vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8):
 // at most n vector memory operations left.
 constexpr int wait_vm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
@@ -255,40 +256,42 @@ __device__ __forceinline__ void attn_tile4(const AttnArgs& a) {
   // P of a step's scores as bf16 pairs, O and l rescaled where the max grew.
   auto softmax = [&](const floatx4& s0, const floatx4& s1, int h0, int h1, uint32_t (&pk)[4]) {
     float sc[8];   // keys 4 lg + e of unit 0, then of unit 1
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      sc[e] = __builtin_fmaf(s0[e], a.scale_log2, nm);
-      sc[4 + e] = __builtin_fmaf(s1[e], a.scale_log2, nm);
-    }
-    if (min(h0, h1) < 16) {
+    auto scaled = [&](float offset) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        if (4 * lg + e >= h0) sc[e] = -INFINITY;
-        if (4 * lg + e >= h1) sc[4 + e] = -INFINITY;
+        sc[e] = __builtin_fmaf(s0[e], a.scale_log2, offset);
+        sc[4 + e] = __builtin_fmaf(s1[e], a.scale_log2, offset);
       }
-    }
+      if (min(h0, h1) < 16) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (4 * lg + e >= h0) sc[e] = -INFINITY;
+          if (4 * lg + e >= h1) sc[4 + e] = -INFINITY;
+        }
+      }
+    };
     float ls;
-    auto probs = [&](float shift, bool shifted) {
+    auto probs = [&]() {
       float l0 = 0.f, l1 = 0.f;
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
-        const float x0 = shifted ? sc[2 * p] - shift : sc[2 * p];
-        const float x1 = shifted ? sc[2 * p + 1] - shift : sc[2 * p + 1];
-        const float p0 = __builtin_amdgcn_exp2f(x0), p1 = __builtin_amdgcn_exp2f(x1);
+        const float p0 = __builtin_amdgcn_exp2f(sc[2 * p]), p1 = __builtin_amdgcn_exp2f(sc[2 * p + 1]);
         pk[p] = pack2(p0, p1);
         l0 += p0;   // (v_dot2 on the packed pair would queue with the products: 59 us against 52)
         l1 += p1;
       }
       ls = l0 + l1;
     };
-    probs(0.f, false);
-    // The max grew, or there is none yet: take the step's, rescale, redo.
-    if (__any(!(ls <= kSumLimit) || m_run < -1e29f)) {
+    scaled(nm);
+    probs();
+    // The max grew, or there is none yet: take the step's, rescale, redo (from
+    // the scores: those against the old max are rounded at its distance).
+    if (__any(!(ls <= kSumLimit) || m_run < kNoMax)) {
+      scaled(0.f);
       float mx = sc[0];
 #pragma unroll
       for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sc[e]);
-      const float mb = m_run > -1e29f ? m_run : 0.f;   // the offset in sc
-      const float mabs = mb + xmax4(mx);
+      const float mabs = xmax4(mx);
       if (mabs > m_run) {
         const float alpha = __builtin_amdgcn_exp2f(m_run - mabs);   // 0 while unset
         m_run = mabs;
@@ -296,9 +299,9 @@ __device__ __forceinline__ void attn_tile4(const AttnArgs& a) {
 #pragma unroll
         for (int db = 0; db < NDB; ++db) oacc[db] *= alpha;
       }
-      const float mnew = m_run > -1e29f ? m_run : 0.f;
-      probs(mnew - mb, true);
-      nm = -mnew;
+      nm = m_run > kNoMax ? -m_run : 0.f;
+      scaled(nm);
+      probs();
     }
     l_run += ls;
   };

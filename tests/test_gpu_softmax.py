@@ -1,5 +1,6 @@
 """The running softmax of the bf16 kernels for more than 64 blocks and for 4x4
-blocks: sums of probabilities before their rounding to bf16."""
+blocks: sums of probabilities before their rounding to bf16, and scores far
+below and above the first ones."""
 import numpy as np
 import pytest
 import torch
@@ -7,7 +8,7 @@ import torch
 from oracle import ssba_oracle as O
 from paper_2605_15684_amd.inputs import make_qkv, workload_from
 
-from _parity import gpu_desc, to64
+from _parity import gpu_desc, oracle_kw, to64
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +58,30 @@ def test_row_sums_are_32_bit(w):
     n = w.keep * w.tile * w.tile - 2
     want = torch.tensor((2 + n * 0.5) / (2 + n * p)).to(torch.bfloat16)
     assert want < 1 and bool((out == want).all())
+
+
+@kernels
+def test_a_first_block_far_below(w):
+    """The first list entry's scores lie 10^7 log2 units below the second's,
+    which differ by less than a rounding step of that distance."""
+    q, k, v = make_qkv(w)
+    q[..., 0], k[..., 0] = 1024, 0
+    frame = _frame(w)
+    k[0, 0, frame[0], 0] = -2.0 ** 17
+    if w.tile == 4:   # two blocks a step
+        k[0, 0, frame[1], 0] = -2.0 ** 17
+    out, idx = _run(w, q, k, v)
+    ref = O.attention(to64(q), to64(k), to64(v), idx, **oracle_kw(w))
+    bound = O.attention(to64(q), to64(k), np.abs(to64(v)), idx, **oracle_kw(w)) / 128   # P and the output: 8 bits each
+    assert (np.abs(to64(out) - ref) <= bound).all()
+
+
+@kernels
+def test_all_scores_far_below(w):
+    """Every score is -4.6e29 / -3.2e29 log2 units: equal probabilities, not a row without keys."""
+    q, k, v = make_qkv(w)
+    q[..., 0], k[..., 0] = 2.0 ** 50, -2.0 ** 51
+    out, idx = _run(w, q, k, v)
+    seen = to64(v)[0, 0, _frame(w)[:w.keep].ravel()]
+    bound = np.abs(seen).mean(0) / 256
+    assert (np.abs(to64(out)[0, 0] - seen.mean(0)) <= bound).all()

@@ -250,9 +250,9 @@ __global__ void __launch_bounds__(256) k_pool_keys_layers(PoolLayers p) {
 // rounded products of the pooled query row i0 + r and the pooled key column j.
 // A channel of the keys is loaded once for R query rows, whose own sums come
 // as scalar operands (the rows past the last repeat it).
-// BATCH key loads are in flight at a time: more up to 64 blocks, where a short
-// launch is bound by these round trips and one wave has the registers.
-template <int D, int R, int BATCH>
+// BATCH key loads are in flight at a time.  One row (short launches, bound by
+// these round trips) has the registers for 64, with no drain between batches.
+template <int D, int R>
 __device__ __forceinline__ void affinity_rows(const IndexArgs& a, int64_t bh, int i0, int j, double (&s)[R]) {
   typedef const __attribute__((address_space(4))) double* ConstPtr;   // written before this launch
   const int tb = a.n_tiles;
@@ -260,7 +260,8 @@ __device__ __forceinline__ void affinity_rows(const IndexArgs& a, int64_t bh, in
   ConstPtr q[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) q[r] = (ConstPtr)(a.qb + (bh * tb + min(i0 + r, tb - 1)) * D);
-#pragma unroll 1
+  constexpr int BATCH = R == 1 ? 64 : R == 2 ? 32 : 16;
+#pragma unroll(R == 1 ? D / BATCH : 1)
   for (int c0 = 0; c0 < D; c0 += BATCH) {
     double kv[BATCH];
 #pragma unroll
@@ -274,6 +275,11 @@ __device__ __forceinline__ void affinity_rows(const IndexArgs& a, int64_t bh, in
       }
   }
 }
+
+// Waves a SIMD that the row kernels' registers are made for: one-row launches
+// have fewer than one.
+template <int R>
+constexpr int kRowWaves = R == 1 ? 3 : 8;
 
 // True for the ranking keys of infinities and NaNs.
 __device__ __forceinline__ bool key_nonfinite(uint64_t key) {
@@ -328,13 +334,15 @@ __device__ __forceinline__ bool rank_row(const uint64_t* keys, int tb, int keep,
 
 // One workgroup per R query blocks of a (batch, head): thread j computes
 // S[i][j] of the R rows, then each wave ranks every (number of waves)-th row.
-// What bounds it: the fp64 units (2 D operations an affinity).  One row per
-// workgroup, ranked by counting, read a head's pooled keys from the L2 once
-// per row and compared each key with every other.  Measured at 345 blocks,
-// 12 heads, D 64: 109 us -> 29 us; 256 blocks, 16 heads: 53 -> 17 us; 64
-// blocks, 32 heads, D 128: 13 -> 9 us.
+// What bounds it: round trips for the keys and chains of fp64 sums (345
+// blocks, 12 heads: the 2 D operations an affinity alone would take 5 us of
+// 28).  One row per workgroup, ranked by counting, read a head's pooled keys
+// from the L2 once per row and compared each key with every other.  Measured
+// at 345 blocks, 12 heads, D 64: 109 us -> 29 us; 256 blocks, 16 heads: 53 ->
+// 17 us; 64 blocks, 32 heads, D 128: 13 -> 10 us.
 template <int D, int U, int R>
-__global__ void __launch_bounds__(64 * U) k_gate_topk(IndexArgs a) {
+__global__ void __launch_bounds__(64 * U) __attribute__((amdgpu_waves_per_eu(1, kRowWaves<R>)))
+k_gate_topk(IndexArgs a) {
   extern __shared__ uint64_t keys[];   // [R][T_b]
   const int tb = a.n_tiles, groups = (tb + R - 1) / R;
   int g, h, b;
@@ -343,7 +351,7 @@ __global__ void __launch_bounds__(64 * U) k_gate_topk(IndexArgs a) {
   const int j = threadIdx.x, lane = j & 63, i0 = g * R;
   if (j < tb) {
     double s[R];
-    affinity_rows<D, R, U == 1 ? 32 : 16>(a, bh, i0, j, s);
+    affinity_rows<D, R>(a, bh, i0, j, s);
 #pragma unroll
     for (int r = 0; r < R; ++r) keys[r * tb + j] = rank_key(s[r]);
   }
@@ -368,14 +376,15 @@ __device__ __forceinline__ void affinity_rows_body(const IndexArgs& a) {
   const int i0 = g * R, rows = min(R, tb - i0);
   if (j >= tb) return;
   double s[R];
-  affinity_rows<D, R, U == 1 ? 32 : 16>(a, bh, i0, j, s);
+  affinity_rows<D, R>(a, bh, i0, j, s);
 #pragma unroll
   for (int r = 0; r < R; ++r)
     if (r < rows) a.srows[(bh * tb + i0 + r) * tb + j] = s[r];
 }
 
 template <int D, int U, int R>
-__global__ void __launch_bounds__(64 * U) k_affinity_rows(IndexArgs a) {
+__global__ void __launch_bounds__(64 * U) __attribute__((amdgpu_waves_per_eu(1, kRowWaves<R>)))
+k_affinity_rows(IndexArgs a) {
   affinity_rows_body<D, U, R>(a);
 }
 
@@ -412,13 +421,14 @@ __device__ __forceinline__ void gate_shared_body(const IndexArgs& a) {
     if (j == 0) bad = odd ? 1 : 0;
   }
   __syncthreads();
+  const int entry = j < tb ? list[1 + j] : 0, flag = bad;
   for (int h = 0; h < a.heads; ++h) {
     const int64_t bh = (int64_t)b * a.heads + h;
     int32_t* out = a.index + (bh * tb + i) * (tb + 1);
-    if (j < tb) out[1 + j] = list[1 + j];
+    if (j < tb) out[1 + j] = entry;
     if (j == 0) {
-      out[0] = list[0];
-      a.flags[bh * tb + i] = bad;
+      out[0] = a.keep;
+      a.flags[bh * tb + i] = flag;
     }
   }
 }
@@ -427,9 +437,6 @@ template <int U>
 __global__ void __launch_bounds__(64 * U) k_gate_shared(IndexArgs a) {
   gate_shared_body<U>(a);
 }
-
-// Query rows per workgroup of the layers' affinity launch (one wave each).
-constexpr int kLayerRows = 2;
 
 // The head-shared gate of several layers of one shape, one launch per step
 // (grid y = layer): each workgroup does what it does for its own layer.
@@ -453,9 +460,10 @@ __global__ void __launch_bounds__(256) k_pool_layers(IndexLayers p) {
   pool_block<SSBA_DT_BF16, TILE_LOG2, D, 2>(layer_index_args(p));
 }
 
-template <int D>
-__global__ void __launch_bounds__(64) k_affinity_rows_layers(IndexLayers p) {
-  affinity_rows_body<D, 1, kLayerRows>(layer_index_args(p));
+template <int D, int R>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, kRowWaves<R>)))
+k_affinity_rows_layers(IndexLayers p) {
+  affinity_rows_body<D, 1, R>(layer_index_args(p));
 }
 
 __global__ void __launch_bounds__(64) k_gate_shared_layers(IndexLayers p) {
@@ -560,17 +568,27 @@ void launch_rows(const IndexArgs& a, bool shared, hipStream_t s) {
 }
 
 // The affinity rows of every query block, ranked per head or (shared) stored.
-// Rows per workgroup, measured as gate launches of 1 / 2 / 4 / 8 rows: 345
-// blocks, 12 heads, D 64: 57 / 38 / 29 / 67 us; 256 blocks, 16 heads: 36 / 22 /
-// 17 / 35 us (at 8 the scalar operands spill).  Up to 64 blocks a workgroup
-// is one wave, so fewer rows keep the chip filled: 64 blocks, 32 heads, D
-// 128: 12 / 9 / 17 / 47 us; one row each where even so there are fewer than
-// two waves a SIMD.
+// More rows per workgroup save key reads, fewer keep a short launch spread
+// over the chip and its chains short.  With `waves` the waves of a one-row
+// launch, the index call (pooling and 9 us of launches included) at 1 / 2 / 4
+// rows, D 64 | D 128, us:
+//   72 blocks,  1 head  (144)    10.6 / 11.3 / 15.2 | 11.4 / 11.8 / 20.0
+//   256 blocks, 1 head  (1024)   10.7 / 11.8 / 14.4 | 12.7 / 13.3 / 21.1
+//   256 blocks, 2 heads (2048)   12.4 / 12.5 / 13.8 | 17.2 / 14.0 / 22.1
+//   144 blocks, 16 heads (6912)  22.4 / 16.8 / 18.2 | 34.4 / 23.7 / 22.7
+//   256 blocks, 8 heads (8192)   23.6 / 17.3 / 15.0 | 38.6 / 24.2 / 19.6
+// Head-shared rows are not ranked here, and four pay earlier (144 blocks, 8
+// heads, 3456 waves: 18.4 / 16.2 / 15.0 | 25.9 / 20.3 / 18.3).  Up to 64
+// blocks a workgroup is one wave and four rows lose (64 blocks, 32 heads, D
+// 128: 17 us against 9 for the launch); above 256, four rows lose to two only
+// with one head at D 128 (324 blocks: 21.0 / 16.6 / 18.6).
 template <int D>
 void launch_rows_d(const IndexArgs& a, bool shared, hipStream_t s) {
-  const int64_t rows = (int64_t)a.n_tiles * a.heads * a.batch;
-  if (a.n_tiles <= 64 && rows < 2048) launch_rows<D, 1, 1>(a, shared, s);
-  else if (a.n_tiles <= 64) launch_rows<D, 1, 2>(a, shared, s);
+  const int64_t waves = (int64_t)a.n_tiles * a.heads * a.batch * ((a.n_tiles + 63) / 64);
+  const bool one = waves < 1024, two = waves < (shared ? 3072 : 7168);
+  if (a.n_tiles <= 64) one ? launch_rows<D, 1, 1>(a, shared, s) : launch_rows<D, 1, 2>(a, shared, s);
+  else if (a.n_tiles <= 256 && one) launch_rows<D, 4, 1>(a, shared, s);
+  else if (a.n_tiles <= 256 && two) launch_rows<D, 4, 2>(a, shared, s);
   else if (a.n_tiles <= 256) launch_rows<D, 4, 4>(a, shared, s);
   else if (a.n_tiles <= 512) launch_rows<D, 8, 4>(a, shared, s);
   else launch_rows<D, 16, 4>(a, shared, s);
@@ -602,17 +620,22 @@ hipError_t launch_topk_shared_layers(const IndexLayers& p, int n_layers, hipStre
       p.f[0].tile_log2 != tl || p.f[1].tile_log2 != tl || (a.head_dim != 64 && a.head_dim != 128))
     return hipErrorInvalidValue;
   const dim3 grid_pool(a.n_tiles * a.heads * a.batch, n_layers);
-  const dim3 grid_rows((a.n_tiles + kLayerRows - 1) / kLayerRows * a.heads * a.batch, n_layers), grid_b(a.n_tiles * a.batch, n_layers);
+  // One or two rows a workgroup, as for one layer with this many rows.
+  const bool one = (int64_t)grid_pool.x * n_layers < 1024;
+  const dim3 grid_rows(one ? grid_pool.x : (a.n_tiles + 1) / 2 * a.heads * a.batch, n_layers);
+  const dim3 grid_b(a.n_tiles * a.batch, n_layers);
   const dim3 block_pool(256), block(round_threads(a.n_tiles));
   const size_t lds = key_bytes(a, 1) + sizeof(int32_t) * (size_t)(a.n_tiles + 1);
   if (a.head_dim == 64) {
     if (tl == 3) hipLaunchKernelGGL((k_pool_layers<3, 64>), grid_pool, block_pool, 0, s, p);
     else hipLaunchKernelGGL((k_pool_layers<4, 64>), grid_pool, block_pool, 0, s, p);
-    hipLaunchKernelGGL((k_affinity_rows_layers<64>), grid_rows, block, 0, s, p);
+    if (one) hipLaunchKernelGGL((k_affinity_rows_layers<64, 1>), grid_rows, block, 0, s, p);
+    else hipLaunchKernelGGL((k_affinity_rows_layers<64, 2>), grid_rows, block, 0, s, p);
   } else {
     if (tl == 3) hipLaunchKernelGGL((k_pool_layers<3, 128>), grid_pool, block_pool, 0, s, p);
     else hipLaunchKernelGGL((k_pool_layers<4, 128>), grid_pool, block_pool, 0, s, p);
-    hipLaunchKernelGGL((k_affinity_rows_layers<128>), grid_rows, block, 0, s, p);
+    if (one) hipLaunchKernelGGL((k_affinity_rows_layers<128, 1>), grid_rows, block, 0, s, p);
+    else hipLaunchKernelGGL((k_affinity_rows_layers<128, 2>), grid_rows, block, 0, s, p);
   }
   hipLaunchKernelGGL(k_gate_shared_layers, grid_b, block, lds, s, p);
   return hipGetLastError();

@@ -46,11 +46,31 @@ def test_lists(grid, gate):
 
 
 @pytest.mark.parametrize("gate", ["topk", "topk_shared"])
-def test_lists_of_many_rows(gate):
-    """63 blocks in 34 heads: two rows per workgroup, the last group of one."""
-    w = _w((4, 252), gate=gate, batch=2, heads=17)
+@pytest.mark.parametrize("grid,heads,d", [((4, 252), 17, 64), ((4, 252), 9, 128), ((20, 52), 5, 128), ((60, 68), 4, 64),
+                                          ((60, 68), 4, 128)])
+def test_lists_of_many_rows(grid, heads, d, gate):
+    """Two and four rows per workgroup, the last group short, in 63, 65 and 255
+    blocks (test_lists has one row in 65, two in 255)."""
+    w = _w(grid, gate=gate, batch=2, heads=heads, head_dim=d)
     (q, k, _), _ = inputs(w)
     assert _check(w, q, k) == 0
+
+
+@pytest.mark.parametrize("heads,layers", [(2, 3), (5, 6)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_shared_stack(d, heads, layers):
+    """The layer driver's rows, one and two per workgroup (15 blocks: the last group of one)."""
+    from paper_2605_15684_amd import ssba
+    w = _w((24, 40), gate="topk_shared", tile=8, batch=3 * heads, heads=heads, head_dim=d, n_text=0)
+    stack = [inputs(w.with_(seed=s)) for s in range(layers)]
+    desc = gpu_desc(w, stack[0][1][0])
+    keeps = [1 + 2 * l for l in range(layers)]
+    index, _ = ssba.forward_layers([dict(q=q, k=k, v=v, out=torch.empty_like(q), keep=n)
+                                    for (_, (q, k, v)), n in zip(stack, keeps)], desc)
+    for l, (((q, k, _), _), n) in enumerate(zip(stack, keeps)):
+        kw = oracle_kw(w)
+        kw["shift"] = w.shift if l % 2 == 0 else (-w.shift[0], -w.shift[1])
+        assert np.array_equal(index[l].cpu().numpy(), O.build_index(to64(q), to64(k), gate=w.gate, keep=n, **kw))
 
 
 @pytest.mark.parametrize("grid", [(20, 52), (60, 92), (36, 228)], ids=["65", "345", "513"])

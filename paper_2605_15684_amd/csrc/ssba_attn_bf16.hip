@@ -390,10 +390,10 @@ hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, int tile, hipStream
   if (mfma_supported(head_dim, tile, a.dense != 0, a.n_tiles, a.seq, span) ||
       (!a.dense && mfma_long_supported(head_dim, tile, a.n_tiles, a.seq, span)))
     return launch_attn_mfma(a, head_dim, tile, s);
-  // 4x4 blocks: the wave-per-block kernel is the faster one at every size
-  // (60x92 tokens, 12 heads, keep 54: 565 -> 52 us); the generic kernel keeps
-  // the slices whose byte offsets pass 31 bits.
-  if (tile4_supported(head_dim, tile, a.dense != 0, span)) return launch_attn_tile4(a, head_dim, s);
+  // 4x4 blocks: the wave-per-block kernel is the faster one (60x92 tokens, 12
+  // heads, keep 54: 565 -> 52 us); the generic kernel keeps the slices whose
+  // byte offsets pass 31 bits.
+  if (tile4_supported(a, head_dim, tile)) return launch_attn_tile4(a, head_dim, s);
   if (head_dim == 64) {
     if (tile == 4) return launch_t<64, 2>(a, s);
     if (tile == 8) return launch_t<64, 3>(a, s);

@@ -429,10 +429,9 @@ hipError_t launch_attn_tile4(const AttnArgs& a0, int head_dim, hipStream_t s) {
   if (a.dense || a.f.tile_log2 != 2 || (head_dim != 64 && head_dim != 128)) return hipErrorInvalidValue;
   a.n_text_groups = (a.f.n_text + 15) / 16;
   a.groups_per_tile = (a.n_tiles + kWaves - 1) / kWaves;
-  const int64_t nbh = (int64_t)a.batch * a.heads;
-  const int64_t total = ((nbh * a.n_text_groups + 7) & ~(int64_t)7) + nbh * a.groups_per_tile;
-  if (nbh <= 0) return hipSuccess;
-  if (total > 0x7FFFFFFF) return hipErrorInvalidValue;
+  const int64_t total = tile4_groups(a);
+  if (total <= 0) return hipSuccess;
+  if (total > kMaxGroups256) return hipErrorInvalidValue;
   const dim3 grid((unsigned)total), block(64 * kWaves);
   if (head_dim == 64) hipLaunchKernelGGL((k_attn_bf16<64, 2>), grid, block, 0, s, a);
   else hipLaunchKernelGGL((k_attn_bf16<128, 2>), grid, block, 0, s, a);

@@ -98,7 +98,13 @@ struct AttnArgs {
   // is resident at once, so the waves are prioritised by the chunks they
   // have left (see k_attn_mfma).
   int equalize;
+  // fp32 kernel, set by its launcher: first (batch, head) pair of the launch
+  // and their number.
+  int bh0, n_bh;
 };
+
+// A launch has fewer than 2^32 threads.
+constexpr int64_t kMaxGroups256 = (((int64_t)1 << 32) - 1) / 256;
 
 // Attention of up to kAttnLayersMax layers of one shape in one launch (the
 // layer driver): layer y reads q/k/v[y] and writes o[y] in frame
@@ -222,8 +228,9 @@ hipError_t launch_attn_f32(const AttnArgs& a, int head_dim, int tile, hipStream_
 bool mfma_supported(int head_dim, int tile, bool dense, int n_tiles, int seq, int64_t span);
 // More than 64 blocks of 8x8 or 16x16 tokens, reading an index.
 bool mfma_long_supported(int head_dim, int tile, int n_tiles, int seq, int64_t span);
-// 4x4 blocks, one wave per block.
-bool tile4_supported(int head_dim, int tile, bool dense, int64_t span);
+// 4x4 blocks, one wave per block; the workgroups of its launch.
+int64_t tile4_groups(const AttnArgs& a);
+bool tile4_supported(const AttnArgs& a, int head_dim, int tile);
 hipError_t launch_attn_tile4(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_attn_mfma(const AttnArgs& a, int head_dim, int tile, hipStream_t s);
 // Attention (bf16, D 64 or 128; 8x8 blocks when gated, 8x8 or 16x16 with an

@@ -36,10 +36,18 @@ bool mfma_long_supported(int head_dim, int tile, int n_tiles, int seq, int64_t s
          2 * (span + span / seq * kMfmaChunk) < ((int64_t)1 << 32);
 }
 
-bool tile4_supported(int head_dim, int tile, bool dense, int64_t span) {
+int64_t tile4_groups(const AttnArgs& a) {
+  // 16 text rows a group (a multiple of 8 of them), or four blocks.
+  const int64_t pairs = (int64_t)a.batch * a.heads;
+  return ((pairs * ((a.f.n_text + 15) / 16) + 7) & ~(int64_t)7) + pairs * ((a.n_tiles + 3) / 4);
+}
+
+bool tile4_supported(const AttnArgs& a, int head_dim, int tile) {
   // Byte offsets inside one (batch, head) below 2^31: the next value up marks
-  // a row that is not there.
-  return (head_dim == 64 || head_dim == 128) && tile == 4 && !dense && 2 * span < ((int64_t)1 << 31);
+  // a row that is not there.  Its groups of few blocks or rows take up to four
+  // times the threads of the generic kernel, which keeps what passes a launch.
+  return (head_dim == 64 || head_dim == 128) && tile == 4 && !a.dense &&
+         2 * (int64_t)a.seq * a.st < ((int64_t)1 << 31) && tile4_groups(a) <= kMaxGroups256;
 }
 
 const char* attn_kernel_name(const AttnArgs& a, int head_dim, int tile, int dtype) {

@@ -599,7 +599,7 @@ ssba_status ssba_forward_layers_ex(const ssba_desc* d, const ssba_layer* layers,
     return SSBA_OK;
   }
   int cached[2] = {-1, -1};   // static gates: the layer whose index serves each parity
-  if (d->dtype == SSBA_DT_BF16 &&
+  if (d->dtype == SSBA_DT_BF16 && d->gate != SSBA_GATE_TOPK &&
       ssba::mfma_supported(d->head_dim, d->tile, false, s.n_tiles, s.seq, (int64_t)s.seq * s.st)) {
     // Each layer's index as one call per layer builds it (the head-shared
     // top-k gate of up to 32 layers in one launch per step, a static gate

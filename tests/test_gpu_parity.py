@@ -457,7 +457,7 @@ def test_layer_stack_equals_per_layer_calls(gate, window):
             assert ssba.read_status(dl_status, scratch[l]) == 0
 
 
-@pytest.mark.parametrize("gate,window", [("window", (2, 2)), ("topk_shared", (1, 1))])
+@pytest.mark.parametrize("gate,window", [("window", (2, 2)), ("topk_shared", (1, 1)), ("topk", (1, 1))])
 def test_layer_stack_16x16_blocks_d128(gate, window):
     """The layer driver's one attention launch over several layers with
     16x16 blocks at head_dim 128 (the 128x128-grid kernels): every layer's
@@ -476,7 +476,7 @@ def test_layer_stack_16x16_blocks_d128(gate, window):
             continue
         wl = w.with_(shift=(8, 8) if l % 2 == 0 else (-8, -8), keep=keeps[l])
         dl = gpu_desc(wl, L["q"])
-        if gate == "topk_shared":
+        if gate in ("topk", "topk_shared"):
             idx1, _ = ssba.build_index(L["q"], L["k"], dl)
             assert torch.equal(index[l], idx1), f"layer {l}"
         else:

@@ -107,7 +107,8 @@ def kernel_sources(kernel: str):
     stem = kernel.split("<")[0]
     if stem in ("k_haar_dwt", "k_haar_iwt"):
         return [os.path.join(base, "ssba_haar.hip"), os.path.join(ROOT, "include", "ssba_haar.h")]
-    own = {"k_attn_mfma": "ssba_attn_mfma.hip", "k_attn_bf16": "ssba_attn_bf16.hip",
+    own = {"k_attn_mfma": "ssba_attn_mfma.hip", "k_attn_mfma_long": "ssba_attn_mfma.hip",
+           "k_attn_tile4": "ssba_attn_tile4.hip", "k_attn_bf16": "ssba_attn_bf16.hip",
            "k_attn_f32": "ssba_attn_f32.hip"}[stem]
     return [os.path.join(base, own), os.path.join(base, "ssba_common.h"),
             os.path.join(ROOT, "include", "ssba.h")]

@@ -413,12 +413,9 @@ __device__ __forceinline__ void attn_tile4(const AttnArgs& a) {
   }
 }
 
-// (Shares its name with the generic kernel's 4x4 instance, which serves the
-// slices of 2 GiB and more.)
-template <int D, int TILE_LOG2>
+template <int D>
 __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(D == 64 ? 5 : 2)))
-k_attn_bf16(AttnArgs a) {
-  static_assert(TILE_LOG2 == 2, "a unit of 16 keys is one 4x4 block");
+k_attn_tile4(AttnArgs a) {
   attn_tile4<D>(a);
 }
 
@@ -433,8 +430,8 @@ hipError_t launch_attn_tile4(const AttnArgs& a0, int head_dim, hipStream_t s) {
   if (total <= 0) return hipSuccess;
   if (total > kMaxGroups256) return hipErrorInvalidValue;
   const dim3 grid((unsigned)total), block(64 * kWaves);
-  if (head_dim == 64) hipLaunchKernelGGL((k_attn_bf16<64, 2>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((k_attn_bf16<128, 2>), grid, block, 0, s, a);
+  if (head_dim == 64) hipLaunchKernelGGL((k_attn_tile4<64>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k_attn_tile4<128>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 

@@ -59,6 +59,7 @@ const char* attn_kernel_name(const AttnArgs& a, int head_dim, int tile, int dtyp
                                             {"k_attn_mfma_long<128, 3>", "k_attn_mfma_long<128, 4>"}};
     return longs[head_dim == 64 ? 0 : 1][tile == 16 ? 1 : 0];
   }
+  if (tile4_supported(a, head_dim, tile)) return head_dim == 64 ? "k_attn_tile4<64>" : "k_attn_tile4<128>";
   static const char* const names[2][3] = {
       {"k_attn_bf16<64, 2>", "k_attn_bf16<64, 3>", "k_attn_bf16<64, 4>"},
       {"k_attn_bf16<128, 2>", "k_attn_bf16<128, 3>", "k_attn_bf16<128, 4>"}};

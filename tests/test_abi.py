@@ -124,7 +124,7 @@ def test_misaligned_pointers_rejected(lib):
     ({"grid_h": 128, "grid_w": 128, "tile": 16, "head_dim": 128, "keep": 7}, True, "k_attn_mfma<128, 3, true, false>"),
     ({"grid_h": 64, "grid_w": 64, "tile": 16, "keep": 4}, False, "k_attn_mfma<64, 4, false, false>"),
     ({"grid_h": 16, "grid_w": 16, "tile": 4, "keep": 4, "dtype": _lib.DT_F32}, False, "k_attn_f32<64>"),
-    ({"grid_h": 32, "grid_w": 32, "tile": 4, "keep": 4}, False, "k_attn_bf16<64, 2>"),
+    ({"grid_h": 32, "grid_w": 32, "tile": 4, "keep": 4}, False, "k_attn_tile4<64>"),
 ])
 def test_forward_kernel_names(lib, kw, dense, name):
     assert _lib.forward_kernel(_desc(**kw), dense) == name

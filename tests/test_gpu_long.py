@@ -121,8 +121,13 @@ def test_kernel_names():
     assert d() == "k_attn_mfma_long<64, 3>"
     assert d(tile=16, grid_h=128, grid_w=256, head_dim=128) == "k_attn_mfma_long<128, 4>"
     assert d(grid_w=64) == "k_attn_mfma<64, 3, false, false>"
-    assert d(tile=4) == "k_attn_bf16<64, 2>"
-    # 32-bit byte offsets inside one (batch, head) are the kernel's limit
+    assert d(tile=4) == "k_attn_tile4<64>"
+    assert d(tile=4, head_dim=128, dtype=_lib.DT_F32) == "k_attn_f32<128>"
+    assert d(tile=4, grid_h=4, grid_w=4, keep=1, batch=(1 << 24) - 1) == "k_attn_tile4<64>"     # 2^32 threads
+    assert d(tile=4, grid_h=4, grid_w=4, keep=1, batch=1 << 24) == "k_attn_bf16<64, 2>"
+    # 32-bit (4x4: 31-bit) byte offsets inside one (batch, head) are the kernels' limits
+    assert d(tile=4, stride_b=1 << 40, stride_h=1 << 36, stride_t=233016) == "k_attn_tile4<64>"
+    assert d(tile=4, stride_b=1 << 40, stride_h=1 << 36, stride_t=233024) == "k_attn_bf16<64, 2>"
     assert d(stride_b=1 << 40, stride_h=1 << 36, stride_t=1 << 20) == "k_attn_bf16<64, 3>"
 
 

@@ -1,7 +1,7 @@
 """Limits and degenerate shapes on the GPU, against the oracle: the largest
 block count the index supports (1024 blocks: a 128x128 grid of 4x4 tiles),
 a grid that is a single block (every key kept), and a sequence shorter than
-one 64-key chunk (the generic kernels)."""
+one 64-key chunk."""
 import numpy as np
 import pytest
 
@@ -23,7 +23,7 @@ CASES = [
                   n_text=3, gate="topk", keep=1, shift=(4, 4), seed=23),
     workload_from(name="one_block_f32", batch=1, heads=2, grid_h=16, grid_w=16, head_dim=128, tile=16,
                   gate="topk", keep=1, dtype="f32", seed=24),
-    # 32 tokens in all: shorter than one 64-key chunk of the MFMA kernels
+    # 32 tokens in all: two of the 4x4 kernel's units, fewer than a 64-key chunk
     workload_from(name="short_seq", batch=1, heads=3, grid_h=4, grid_w=8, head_dim=64, tile=4,
                   gate="topk", keep=1, shift=(1, 2), seed=25),
 ]

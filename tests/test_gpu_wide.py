@@ -25,8 +25,8 @@ def _w(**kw):
 
 # workload, bytes that a slice (with this many rows more) has to stay below, kernels at and past the limit
 CASES = [
-    (_w(), 1 << 31, 0, "k_attn_bf16<64, 2>", "k_attn_bf16<64, 2>"),
-    (_w(head_dim=128), 1 << 31, 0, "k_attn_bf16<128, 2>", "k_attn_bf16<128, 2>"),
+    (_w(), 1 << 31, 0, "k_attn_tile4<64>", "k_attn_bf16<64, 2>"),
+    (_w(head_dim=128), 1 << 31, 0, "k_attn_tile4<128>", "k_attn_bf16<128, 2>"),
     (_w(grid_h=72, grid_w=72, tile=8, keep=9), 1 << 32, 64, "k_attn_mfma_long<64, 3>", "k_attn_bf16<64, 3>"),
     (_w(grid_h=72, grid_w=72, tile=8, keep=66, head_dim=128, n_text=77), 1 << 32, 64, "k_attn_mfma_long<128, 3>",
      "k_attn_bf16<128, 3>"),

@@ -496,7 +496,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
   // (batch, head) and group: consecutive hardware ids go round-robin over the
   // 8 XCDs; when the (batch, head) count divides by 8 each XCD gets whole
   // heads, so their K and V stay in its L2.  Text groups (every key) first.
-  const int bid = blockIdx.x, nbh = a.n_bh, nt = a.n_text_groups, ni = a.groups_per_bh - nt;
+  const int bid = blockIdx.x, nbh = a.batch * a.heads, nt = a.n_text_groups, ni = a.groups_per_bh - nt;
   int bh, r;
   if ((nbh & 7) == 0) {
     const int xcd = bid & 7, s = bid >> 3, hpx = nbh >> 3;
@@ -508,7 +508,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 6
     bh = bid / a.groups_per_bh;
     r = bid - bh * a.groups_per_bh;
   }
-  bh += a.bh0;
   const int b = bh / a.heads, h = bh - b * a.heads;
   const int64_t off = (int64_t)b * a.sb + (int64_t)h * a.sh;
   if (r < nt) {
@@ -532,19 +531,26 @@ hipError_t launch_t(const AttnArgs& a0, int tile, hipStream_t s) {
     a.n_text_groups = (a.f.n_text + 15) / 16;
     a.groups_per_bh = a.n_text_groups + (tile == 4 ? (a.n_tiles + 3) / 4 : tile == 8 ? a.n_tiles : 4 * a.n_tiles);
   }
-  // As many (batch, head) pairs to a launch as it has threads for (one launch
-  // but for millions of pairs); a multiple of 8, for the XCDs.
-  const int64_t pairs = (int64_t)a.batch * a.heads;
+  // One launch, but for millions of (batch, head) pairs: whole batch elements,
+  // or heads of one, as many as a launch has threads for.
   int64_t per = kMaxGroups256 / a.groups_per_bh;
-  if (per > 8) per &= ~(int64_t)7;
   if (per < 1) per = 1;
-  for (int64_t p = 0; p < pairs; p += per) {
-    a.bh0 = (int)p;
-    a.n_bh = (int)(pairs - p < per ? pairs - p : per);
-    hipLaunchKernelGGL(k_attn_f32<D>, dim3((unsigned)a.n_bh * (unsigned)a.groups_per_bh), dim3(256), 0, s, a);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
+  const int64_t nb = per / a0.heads > 0 ? per / a0.heads : 1, nh = per < a0.heads ? per : a0.heads;
+  for (int64_t b = 0; b < a0.batch; b += nb)
+    for (int64_t h = 0; h < a0.heads; h += nh) {
+      const int64_t off = b * a.sb + h * a.sh;
+      a.batch = (int)(a0.batch - b < nb ? a0.batch - b : nb);
+      a.heads = (int)(a0.heads - h < nh ? a0.heads - h : nh);
+      a.q = static_cast<const float*>(a0.q) + off;
+      a.k = static_cast<const float*>(a0.k) + off;
+      a.v = static_cast<const float*>(a0.v) + off;
+      a.o = static_cast<float*>(a0.o) + off;
+      if (!a.dense) a.index = a0.index + (b * a0.heads + h) * a.n_tiles * (a.n_tiles + 1);
+      const int64_t total = (int64_t)a.batch * a.heads * a.groups_per_bh;
+      hipLaunchKernelGGL(k_attn_f32<D>, dim3((unsigned)total), dim3(256), 0, s, a);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   return hipSuccess;
 }
 

@@ -98,9 +98,6 @@ struct AttnArgs {
   // is resident at once, so the waves are prioritised by the chunks they
   // have left (see k_attn_mfma).
   int equalize;
-  // fp32 kernel, set by its launcher: first (batch, head) pair of the launch
-  // and their number.
-  int bh0, n_bh;
 };
 
 // A launch has fewer than 2^32 threads.

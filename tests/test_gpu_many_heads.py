@@ -10,10 +10,12 @@ pytestmark = pytest.mark.gpu
 PAIRS = (1 << 24) + 8
 
 
-@pytest.mark.parametrize("dtype,step", [(torch.float32, 4), (torch.bfloat16, 8)], ids=["f32", "bf16"])
-def test_last_pair(dtype, step):
+@pytest.mark.parametrize("dtype,step,batch", [(torch.float32, 4, PAIRS // 8), (torch.float32, 4, 1),
+                                              (torch.bfloat16, 8, PAIRS // 8)], ids=["f32", "f32-heads", "bf16"])
+def test_last_pair(dtype, step, batch):
     from paper_2605_15684_amd import ssba
-    shape, strides = (PAIRS // 8, 8, 16, 64), (8 * step, step, 64, 1)
+    heads = PAIRS // batch
+    shape, strides = (batch, heads, 16, 64), (heads * step, step, 64, 1)
     mk = lambda x: torch.full(((PAIRS - 1) * step + 1024,), x, dtype=dtype, device="cuda")   # noqa: E731
     q, buf = torch.as_strided(mk(0.5), shape, strides), mk(-1.0)
     desc = ssba.desc_for(q, grid=(4, 4), tile=4, gate="dense")

@@ -525,12 +525,14 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
   auto copy = [&](const __amdgpu_buffer_rsrc_t& rs, const Chunk& ch, char* dst, bool is_k) {
     int lb = HALF * sk + 1024 * NIW * qh;
     asm volatile("" : "+s"(lb));
+    unsigned k0 = kcol[0];   // LONG at D 128 holds one column offset, as in values()
+    if constexpr (LONG && D == 128) asm volatile("" : "+v"(k0));
 #pragma unroll
     for (int mm = 0; mm < NIW; ++mm) {
       const int m = NIW * qh + mm;
       const int rr = (KPI * m) / BT;   // block row of the instruction within the half
       const int row = ch.row0 + rr * ch.rstep + (ch.y0 + rr < 0 ? wrap : 0);
-      const unsigned col = is_k ? kcol[mm] : vcol;
+      const unsigned col = !is_k ? vcol : LONG && D == 128 ? k0 ^ (64u * mm) : kcol[mm];
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(dst + lb + 1024 * mm), 16,
                                                ch.lane_off[mm] + col, 2u * (unsigned)row * (unsigned)st, 0, 0);
     }
@@ -556,16 +558,16 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
   uint32_t pk[8];   // P of the current chunk, bf16 pairs
   auto scores = [&](const char* kt, int lo, int hi) {
     // S^T = K . Q^T: the lane's 16 keys 8 (r / 4) + 4 hw + r % 4 of its query.
-    floatx16 sc;   // s - m_run: the exponent of exp2
     auto products = [&]() {
-      sc = kSeed ? negm : floatx16{};
+      floatx16 s = kSeed ? negm : floatx16{};
 #pragma unroll
       for (int ks = 0; ks < NKS; ++ks) {
         const bf16x8 kf = *reinterpret_cast<const bf16x8*>(kt + koff[ks]);
-        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], sc, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s, 0, 0, 0);
       }
+      return s;
     };
-    products();
+    floatx16 sc = products();   // s - m_run: the exponent of exp2
     if constexpr (LONG) {
 #pragma unroll
       for (int rr = 0; rr < 16; ++rr) sc[rr] = __builtin_fmaf(sc[rr], a.scale_log2, nm);
@@ -574,17 +576,15 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
       for (int rr = 0; rr < 16; ++rr) sc[rr] += nm;
     }
     auto mask = [&]() {
-      if (lo > 0 || hi < KH) {   // rare: ragged chunk or invalid block id
-        int l4 = lo - 4 * hw, h4 = hi - 4 * hw;
-        asm volatile("" : "+v"(l4), "+v"(h4));
+      int l4 = lo - 4 * hw, h4 = hi - 4 * hw;
+      asm volatile("" : "+v"(l4), "+v"(h4));
 #pragma unroll
-        for (int rr = 0; rr < 16; ++rr) {
-          const int key = 8 * (rr >> 2) + (rr & 3);   // minus 4 * hw
-          if (key < l4 || key >= h4) sc[rr] = -INFINITY;
-        }
+      for (int rr = 0; rr < 16; ++rr) {
+        const int key = 8 * (rr >> 2) + (rr & 3);   // minus 4 * hw
+        if (key < l4 || key >= h4) sc[rr] = -INFINITY;
       }
     };
-    mask();
+    if (lo > 0 || hi < KH) mask();   // rare: ragged chunk or invalid block id
     // P = exp2(sc - shift) as bf16 pairs and the lane's sum of the rounded P;
     // LONG: of P as it was in 32 bits (shift is 0 except when a chunk is redone).
     float ls;
@@ -611,23 +611,25 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
       float mx = sc[0];
 #pragma unroll
       for (int rr = 1; rr < 16; ++rr) mx = fmaxf(mx, sc[rr]);
-      const float mb = m_run > kNoMax ? m_run : 0.f;   // the offset in sc
-      float mabs = mb + swap_max(mx);
-      // LONG: where the max is more than 2^10 from that offset, sc was rounded
-      // to worse than 2^-14, and the scores are formed again (K is still in
-      // its buffer).  D 128 always does so: the other path costs it spills.
-      bool again = false;
+      float mb = m_run > kNoMax ? m_run : 0.f;   // the offset in sc
+      // LONG: where the max is more than 2^10 from the offset, sc was rounded
+      // to worse than 2^-14: the scores are formed again (K is still in its
+      // buffer) against an offset near it.  D 128 always does so: the branch
+      // costs it spills.
       if constexpr (LONG) {
-        again = D == 128 || __any(fabsf(mx) > 1024.f && mx > -INFINITY);
-        if (again) {
-          products();
-          mask();
+        if (D == 128 || __any(fabsf(mx) > 1024.f && mx > -INFINITY)) {
+          const float by = swap_max(mx);
+          mb += by > -INFINITY ? by : 0.f;
+          sc = products();
+#pragma unroll
+          for (int rr = 0; rr < 16; ++rr) sc[rr] = __builtin_fmaf(sc[rr], a.scale_log2, -mb);
+          if (hi < KH) mask();
           mx = sc[0];
 #pragma unroll
           for (int rr = 1; rr < 16; ++rr) mx = fmaxf(mx, sc[rr]);
-          mabs = swap_max(mx) * a.scale_log2;
         }
       }
+      const float mabs = mb + swap_max(mx);
       if (mabs > m_run) {
         const float alpha = __builtin_amdgcn_exp2f(m_run - mabs);   // 0 while unset
         m_run = mabs;
@@ -636,13 +638,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
         for (int db = 0; db < NDB; ++db) oacc[db] *= alpha;
       }
       const float mnew = m_run > kNoMax ? m_run : 0.f;
-      if (again) {
-#pragma unroll
-        for (int rr = 0; rr < 16; ++rr) sc[rr] = __builtin_fmaf(sc[rr], a.scale_log2, -mnew);
-        probs(0.f, false);
-      } else {
-        probs(mnew - mb, true);
-      }
+      probs(mnew - mb, true);
       if constexpr (kSeed) {
 #pragma unroll
         for (int rr = 0; rr < 16; ++rr) negm[rr] = -mnew;

@@ -256,42 +256,55 @@ __device__ __forceinline__ void attn_tile4(const AttnArgs& a) {
   // P of a step's scores as bf16 pairs, O and l rescaled where the max grew.
   auto softmax = [&](const floatx4& s0, const floatx4& s1, int h0, int h1, uint32_t (&pk)[4]) {
     float sc[8];   // keys 4 lg + e of unit 0, then of unit 1
-    auto scaled = [&](float offset) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sc[e] = __builtin_fmaf(s0[e], a.scale_log2, nm);
+      sc[4 + e] = __builtin_fmaf(s1[e], a.scale_log2, nm);
+    }
+    if (min(h0, h1) < 16) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        sc[e] = __builtin_fmaf(s0[e], a.scale_log2, offset);
-        sc[4 + e] = __builtin_fmaf(s1[e], a.scale_log2, offset);
+        if (4 * lg + e >= h0) sc[e] = -INFINITY;
+        if (4 * lg + e >= h1) sc[4 + e] = -INFINITY;
       }
-      if (min(h0, h1) < 16) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (4 * lg + e >= h0) sc[e] = -INFINITY;
-          if (4 * lg + e >= h1) sc[4 + e] = -INFINITY;
-        }
-      }
-    };
+    }
     float ls;
-    auto probs = [&]() {
+    auto probs = [&](float shift, bool shifted) {
       float l0 = 0.f, l1 = 0.f;
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
-        const float p0 = __builtin_amdgcn_exp2f(sc[2 * p]), p1 = __builtin_amdgcn_exp2f(sc[2 * p + 1]);
+        const float x0 = shifted ? sc[2 * p] - shift : sc[2 * p];
+        const float x1 = shifted ? sc[2 * p + 1] - shift : sc[2 * p + 1];
+        const float p0 = __builtin_amdgcn_exp2f(x0), p1 = __builtin_amdgcn_exp2f(x1);
         pk[p] = pack2(p0, p1);
         l0 += p0;   // (v_dot2 on the packed pair would queue with the products: 59 us against 52)
         l1 += p1;
       }
       ls = l0 + l1;
     };
-    scaled(nm);
-    probs();
-    // The max grew, or there is none yet: take the step's, rescale, redo (from
-    // the scores: those against the old max are rounded at its distance).
+    probs(0.f, false);
+    // The max grew, or there is none yet: take the step's, rescale, redo.
     if (__any(!(ls <= kSumLimit) || m_run < kNoMax)) {
-      scaled(0.f);
       float mx = sc[0];
 #pragma unroll
       for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sc[e]);
-      const float mabs = xmax4(mx);
+      float mb = m_run > kNoMax ? m_run : 0.f;   // the offset in sc
+      // Where the max is more than 2^10 from the offset, sc was rounded to
+      // worse than 2^-14: again from the scores, against an offset near it.
+      if (__any(fabsf(mx) > 1024.f && mx > -INFINITY)) {
+        const float by = xmax4(mx);
+        mb += by > -INFINITY ? by : 0.f;
+        int g0 = h0, g1 = h1;   // (opaque, or the tests of h0 and h1 are kept for here)
+        asm volatile("" : "+s"(g0), "+s"(g1));
+        mx = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          sc[e] = 4 * lg + e < g0 ? __builtin_fmaf(s0[e], a.scale_log2, -mb) : -INFINITY;
+          sc[4 + e] = 4 * lg + e < g1 ? __builtin_fmaf(s1[e], a.scale_log2, -mb) : -INFINITY;
+          mx = fmaxf(mx, fmaxf(sc[e], sc[4 + e]));
+        }
+      }
+      const float mabs = mb + xmax4(mx);
       if (mabs > m_run) {
         const float alpha = __builtin_amdgcn_exp2f(m_run - mabs);   // 0 while unset
         m_run = mabs;
@@ -299,9 +312,9 @@ __device__ __forceinline__ void attn_tile4(const AttnArgs& a) {
 #pragma unroll
         for (int db = 0; db < NDB; ++db) oacc[db] *= alpha;
       }
-      nm = m_run > kNoMax ? -m_run : 0.f;
-      scaled(nm);
-      probs();
+      const float mnew = m_run > kNoMax ? m_run : 0.f;
+      probs(mnew - mb, true);
+      nm = -mnew;
     }
     l_run += ls;
   };

@@ -250,8 +250,8 @@ __global__ void __launch_bounds__(256) k_pool_keys_layers(PoolLayers p) {
 // rounded products of the pooled query row i0 + r and the pooled key column j.
 // A channel of the keys is loaded once for R query rows, whose own sums come
 // as scalar operands (the rows past the last repeat it).
-// BATCH key loads are in flight at a time.  One row (short launches, bound by
-// these round trips) has the registers for 64, with no drain between batches.
+// Several rows take BATCH key loads at a time; one row (short launches, bound
+// by these round trips) keeps its loads rolling over all channels.
 template <int D, int R>
 __device__ __forceinline__ void affinity_rows(const IndexArgs& a, int64_t bh, int i0, int j, double (&s)[R]) {
   typedef const __attribute__((address_space(4))) double* ConstPtr;   // written before this launch
@@ -275,11 +275,6 @@ __device__ __forceinline__ void affinity_rows(const IndexArgs& a, int64_t bh, in
       }
   }
 }
-
-// Waves a SIMD that the row kernels' registers are made for: one-row launches
-// have fewer than one.
-template <int R>
-constexpr int kRowWaves = R == 1 ? 3 : 8;
 
 // True for the ranking keys of infinities and NaNs.
 __device__ __forceinline__ bool key_nonfinite(uint64_t key) {
@@ -341,7 +336,7 @@ __device__ __forceinline__ bool rank_row(const uint64_t* keys, int tb, int keep,
 // at 345 blocks, 12 heads, D 64: 109 us -> 29 us; 256 blocks, 16 heads: 53 ->
 // 17 us; 64 blocks, 32 heads, D 128: 13 -> 10 us.
 template <int D, int U, int R>
-__global__ void __launch_bounds__(64 * U) __attribute__((amdgpu_waves_per_eu(1, kRowWaves<R>)))
+__global__ void __launch_bounds__(64 * U)
 k_gate_topk(IndexArgs a) {
   extern __shared__ uint64_t keys[];   // [R][T_b]
   const int tb = a.n_tiles, groups = (tb + R - 1) / R;
@@ -349,6 +344,22 @@ k_gate_topk(IndexArgs a) {
   unit_of(a, groups, g, h, b);
   const int64_t bh = (int64_t)b * a.heads + h;
   const int j = threadIdx.x, lane = j & 63, i0 = g * R;
+  if constexpr (U == 1 && R == 1) {   // one wave, one row: the keys stay in their lanes
+    double s[1] = {0.0};
+    if (j < tb) affinity_rows<D, 1>(a, bh, g, j, s);
+    const uint64_t key = j < tb ? rank_key(s[0]) : 0;
+    const bool kept = wave_topk(key, j < tb, a.keep, lane);
+    const uint64_t km = __builtin_amdgcn_ballot_w64(kept);
+    const bool bad = __builtin_amdgcn_ballot_w64(j < tb && key_nonfinite(key)) != 0;
+    int32_t* out = a.index + (bh * tb + g) * (tb + 1);
+    if (kept) out[1 + __popcll(km & ((1ull << lane) - 1ull))] = j;
+    if (j < tb && j >= a.keep) out[1 + j] = -1;
+    if (j == 0) {
+      out[0] = a.keep;
+      a.flags[bh * tb + g] = bad ? 1 : 0;
+    }
+    return;
+  }
   if (j < tb) {
     double s[R];
     affinity_rows<D, R>(a, bh, i0, j, s);
@@ -383,7 +394,7 @@ __device__ __forceinline__ void affinity_rows_body(const IndexArgs& a) {
 }
 
 template <int D, int U, int R>
-__global__ void __launch_bounds__(64 * U) __attribute__((amdgpu_waves_per_eu(1, kRowWaves<R>)))
+__global__ void __launch_bounds__(64 * U)
 k_affinity_rows(IndexArgs a) {
   affinity_rows_body<D, U, R>(a);
 }
@@ -461,7 +472,7 @@ __global__ void __launch_bounds__(256) k_pool_layers(IndexLayers p) {
 }
 
 template <int D, int R>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, kRowWaves<R>)))
+__global__ void __launch_bounds__(64)
 k_affinity_rows_layers(IndexLayers p) {
   affinity_rows_body<D, 1, R>(layer_index_args(p));
 }
@@ -567,25 +578,36 @@ void launch_rows(const IndexArgs& a, bool shared, hipStream_t s) {
   else hipLaunchKernelGGL((k_gate_topk<D, U, R>), grid, block, key_bytes(a, R), s, a);
 }
 
+// One row per workgroup below this many waves (measured below).
+template <int D>
+constexpr int kOneRow = D == 64 ? 2048 : 1024;
+
 // The affinity rows of every query block, ranked per head or (shared) stored.
 // More rows per workgroup save key reads, fewer keep a short launch spread
 // over the chip and its chains short.  With `waves` the waves of a one-row
-// launch, the index call (pooling and 9 us of launches included) at 1 / 2 / 4
-// rows, D 64 | D 128, us:
-//   72 blocks,  1 head  (144)    10.6 / 11.3 / 15.2 | 11.4 / 11.8 / 20.0
-//   256 blocks, 1 head  (1024)   10.7 / 11.8 / 14.4 | 12.7 / 13.3 / 21.1
-//   256 blocks, 2 heads (2048)   12.4 / 12.5 / 13.8 | 17.2 / 14.0 / 22.1
-//   144 blocks, 16 heads (6912)  22.4 / 16.8 / 18.2 | 34.4 / 23.7 / 22.7
-//   256 blocks, 8 heads (8192)   23.6 / 17.3 / 15.0 | 38.6 / 24.2 / 19.6
-// Head-shared rows are not ranked here, and four pay earlier (144 blocks, 8
-// heads, 3456 waves: 18.4 / 16.2 / 15.0 | 25.9 / 20.3 / 18.3).  Up to 64
-// blocks a workgroup is one wave and four rows lose (64 blocks, 32 heads, D
-// 128: 17 us against 9 for the launch); above 256, four rows lose to two only
-// with one head at D 128 (324 blocks: 21.0 / 16.6 / 18.6).
+// launch, the gate launch at 1 / 2 / 4 rows, us (x: not run there):
+//   D 64:   64 blocks, 16 heads  (1024)   5.5 /  6.6 /    x
+//           64 blocks, 24 heads  (1536)   6.6 /  7.1 /    x
+//           64 blocks, 48 heads  (3072)   9.6 /  8.9 /    x
+//           72 blocks,  4 heads   (576)   6.7 /    x / 12.9
+//          144 blocks, 16 heads  (6912)     x / 13.4 / 14.4
+//          256 blocks,  4 heads  (4096)     x / 11.1 / 12.4
+//   D 128:  64 blocks, 16 heads  (1024)   7.4 /  7.6 /    x
+//           64 blocks, 24 heads  (1536)   9.6 /  8.5 /    x
+//          144 blocks,  1 head    (432)   8.0 /    x / 19.7
+//          144 blocks, 16 heads  (6912)     x / 20.5 / 18.8
+//          256 blocks,  4 heads  (4096)     x / 14.1 / 18.7
+// and as whole index calls (with the pooling) 256 blocks, 8 heads (8192), D 64
+// 23.6 / 17.3 / 15.0, D 128 38.6 / 24.2 / 19.6.  Head-shared rows are not
+// ranked here, and four pay earlier (144 blocks, 8 heads, 3456 waves, D 64
+// 18.4 / 16.2 / 15.0, D 128 25.9 / 20.3 / 18.3).  Up to 64 blocks a workgroup is
+// one wave and four rows lose (64 blocks, 32 heads, D 128: 17 us against 9);
+// above 256, four rows lose to two only with one head at D 128 (324 blocks,
+// the call: 21.0 / 16.6 / 18.6).
 template <int D>
 void launch_rows_d(const IndexArgs& a, bool shared, hipStream_t s) {
   const int64_t waves = (int64_t)a.n_tiles * a.heads * a.batch * ((a.n_tiles + 63) / 64);
-  const bool one = waves < 1024, two = waves < (shared ? 3072 : 7168);
+  const bool one = waves < kOneRow<D>, two = waves < (shared ? 3072 : 7168);
   if (a.n_tiles <= 64) one ? launch_rows<D, 1, 1>(a, shared, s) : launch_rows<D, 1, 2>(a, shared, s);
   else if (a.n_tiles <= 256 && one) launch_rows<D, 4, 1>(a, shared, s);
   else if (a.n_tiles <= 256 && two) launch_rows<D, 4, 2>(a, shared, s);
@@ -621,7 +643,7 @@ hipError_t launch_topk_shared_layers(const IndexLayers& p, int n_layers, hipStre
     return hipErrorInvalidValue;
   const dim3 grid_pool(a.n_tiles * a.heads * a.batch, n_layers);
   // One or two rows a workgroup, as for one layer with this many rows.
-  const bool one = (int64_t)grid_pool.x * n_layers < 1024;
+  const bool one = (int64_t)grid_pool.x * n_layers < (a.head_dim == 64 ? kOneRow<64> : kOneRow<128>);
   const dim3 grid_rows(one ? grid_pool.x : (a.n_tiles + 1) / 2 * a.heads * a.batch, n_layers);
   const dim3 grid_b(a.n_tiles * a.batch, n_layers);
   const dim3 block_pool(256), block(round_threads(a.n_tiles));

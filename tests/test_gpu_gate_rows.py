@@ -46,8 +46,8 @@ def test_lists(grid, gate):
 
 
 @pytest.mark.parametrize("gate", ["topk", "topk_shared"])
-@pytest.mark.parametrize("grid,heads,d", [((4, 252), 17, 64), ((4, 252), 9, 128), ((20, 52), 5, 128), ((60, 68), 4, 64),
-                                          ((60, 68), 4, 128)])
+@pytest.mark.parametrize("grid,heads,d", [((4, 252), 17, 64), ((4, 252), 9, 128), ((20, 52), 5, 128), ((20, 52), 9, 64),
+                                          ((60, 68), 4, 64), ((60, 68), 4, 128)])
 def test_lists_of_many_rows(grid, heads, d, gate):
     """Two and four rows per workgroup, the last group short, in 63, 65 and 255
     blocks (test_lists has one row in 65, two in 255)."""

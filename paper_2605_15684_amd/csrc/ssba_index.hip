@@ -250,8 +250,10 @@ __global__ void __launch_bounds__(256) k_pool_keys_layers(PoolLayers p) {
 // rounded products of the pooled query row i0 + r and the pooled key column j.
 // A channel of the keys is loaded once for R query rows, whose own sums come
 // as scalar operands (the rows past the last repeat it).
-// Several rows take BATCH key loads at a time; one row (short launches, bound
-// by these round trips) keeps its loads rolling over all channels.
+// BATCH key loads are in flight at a time.  One row (short launches, bound by
+// these round trips) keeps them rolling over the 64 channels (12 blocks: 5.0
+// -> 4.0 us the gate launch); over 128 the compiler holds about 20, and batches
+// of 32 are shorter where the sums come from another XCD (32 blocks: 7.6 -> 6.1).
 template <int D, int R>
 __device__ __forceinline__ void affinity_rows(const IndexArgs& a, int64_t bh, int i0, int j, double (&s)[R]) {
   typedef const __attribute__((address_space(4))) double* ConstPtr;   // written before this launch
@@ -260,8 +262,8 @@ __device__ __forceinline__ void affinity_rows(const IndexArgs& a, int64_t bh, in
   ConstPtr q[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) q[r] = (ConstPtr)(a.qb + (bh * tb + min(i0 + r, tb - 1)) * D);
-  constexpr int BATCH = R == 1 ? 64 : R == 2 ? 32 : 16;
-#pragma unroll(R == 1 ? D / BATCH : 1)
+  constexpr int BATCH = R == 1 && D == 64 ? 64 : R <= 2 ? 32 : 16;
+#pragma unroll 1
   for (int c0 = 0; c0 < D; c0 += BATCH) {
     double kv[BATCH];
 #pragma unroll
@@ -580,7 +582,7 @@ void launch_rows(const IndexArgs& a, bool shared, hipStream_t s) {
 
 // One row per workgroup below this many waves (measured below).
 template <int D>
-constexpr int kOneRow = D == 64 ? 2048 : 1024;
+constexpr int kOneRow = D == 64 ? 2048 : 1280;
 
 // The affinity rows of every query block, ranked per head or (shared) stored.
 // More rows per workgroup save key reads, fewer keep a short launch spread
@@ -592,9 +594,9 @@ constexpr int kOneRow = D == 64 ? 2048 : 1024;
 //           72 blocks,  4 heads   (576)   6.7 /    x / 12.9
 //          144 blocks, 16 heads  (6912)     x / 13.4 / 14.4
 //          256 blocks,  4 heads  (4096)     x / 11.1 / 12.4
-//   D 128:  64 blocks, 16 heads  (1024)   7.4 /  7.6 /    x
+//   D 128:  64 blocks, 16 heads  (1024)   7.2 /  8.4 /    x
 //           64 blocks, 24 heads  (1536)   9.6 /  8.5 /    x
-//          144 blocks,  1 head    (432)   8.0 /    x / 19.7
+//          120 blocks,  1 head    (240)   7.7 /    x / 19.2
 //          144 blocks, 16 heads  (6912)     x / 20.5 / 18.8
 //          256 blocks,  4 heads  (4096)     x / 14.1 / 18.7
 // and as whole index calls (with the pooling) 256 blocks, 8 heads (8192), D 64

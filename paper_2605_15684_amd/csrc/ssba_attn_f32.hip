@@ -26,7 +26,7 @@
 // Measured at B 1, H 16, 64x64 tokens, 8x8 blocks, keep 10, D 64 against the
 // one-row-per-thread vector kernel it replaced (the launch alone): 1590 -> 99 us,
 // 109 TFLOP/s (a large fp32 matrix product reaches 154 on this card); at 16x16
-// tokens, 4x4 blocks, 2 heads, keep 4 (one step per launch): 66 -> 7.2 us.
+// tokens, 4x4 blocks, 2 heads, keep 4 (two steps per wave): 66 -> 7.2 us.
 // Relative error against 64 bits at the first size: 6.5e-7 -> 4.3e-7.
 //
 // Register layouts (lane l):

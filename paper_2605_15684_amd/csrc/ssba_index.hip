@@ -18,10 +18,11 @@ namespace ssba {
 namespace {
 
 // (block or group of blocks, head, batch) of a workgroup in a 1-D grid of
-// per_head * heads * batch workgroups.  Consecutive hardware ids go round-robin over the 8 XCDs;
-// when the (batch, head) count divides by 8, each XCD gets whole heads -- the
-// same heads the attention kernel gives it -- so pooled sums, index rows and
-// the head's Q/K stay in one XCD's L2 from kernel to kernel.
+// per_head * heads * batch workgroups.  Consecutive hardware ids go
+// round-robin over the 8 XCDs; when the (batch, head) count divides by 8, each
+// XCD gets whole heads -- the same heads the attention kernel gives it -- so
+// pooled sums, index rows and the head's Q/K stay in one XCD's L2 from kernel
+// to kernel.
 __device__ __forceinline__ void unit_of(const IndexArgs& a, int per_head, int& t, int& h, int& b) {
   const int id = blockIdx.x, nbh = a.batch * a.heads;
   int bh, r;

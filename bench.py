@@ -94,10 +94,10 @@ MEASURED_TRAFFIC = {
     ("k_haar_dwt<unsigned short, 3>", "haar512"): {"sha": "02be9c317bd1aa8b", "fetch_kib": 131115.0,
                                                   "write_kib": 344064.0, "fetch_factor": 1.9998,
                                                   "write_factor": 1.0},
-    ("k_attn_mfma<64, 3, false, true>", "grid64"): {"sha": "c7372682271ec544", "fetch_kib": 12662.5,
+    ("k_attn_mfma<64, 3, false, true>", "grid64"): {"sha": "a2a2784ed1f01a2f", "fetch_kib": 12662.5,
                                                     "write_kib": 8456.0, "fetch_factor": 1.99981,
                                                     "write_factor": 1.0},
-    ("k_attn_mfma<64, 3, false, false>", "grid64"): {"sha": "c7372682271ec544", "fetch_kib": 12554.6,
+    ("k_attn_mfma<64, 3, false, false>", "grid64"): {"sha": "a2a2784ed1f01a2f", "fetch_kib": 12554.6,
                                                      "write_kib": 8192.0, "fetch_factor": 1.99981,
                                                      "write_factor": 1.0},
 }

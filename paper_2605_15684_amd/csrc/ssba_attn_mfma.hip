@@ -388,12 +388,16 @@ __device__ __forceinline__ void attn_mfma_body(const AttnArgs& a) {
   const __amdgpu_buffer_rsrc_t rk =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<u16*>(kbase), (short)0, (int)slice_bytes, kRawBufferFlags);
 
+  const __amdgpu_buffer_rsrc_t rv =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<u16*>(vbase), (short)0, (int)slice_bytes, kRawBufferFlags);
   // V resource of a chunk.  LONG ends it before the keys that are not there,
   // which arrive as zeros: a masked key adds exactly nothing, whatever value
   // the row in its place holds.
   auto values_of = [&](const Chunk& ch) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<u16*>(vbase), (short)0,
-                                             (int)(LONG ? ch.v_bytes : slice_bytes), kRawBufferFlags);
+    if constexpr (LONG)
+      return __builtin_amdgcn_make_buffer_rsrc(const_cast<u16*>(vbase), (short)0, (int)ch.v_bytes, kRawBufferFlags);
+    else
+      return rv;
   };
 
   // DMA lane mapping: lane l of copy instruction m fills key KPI m + l / CPR
